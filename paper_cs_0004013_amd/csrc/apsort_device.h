@@ -107,6 +107,29 @@ __device__ __forceinline__ uint32_t rank_slot(uint32_t* cnt, uint32_t v) {
   return __hip_atomic_fetch_add(&cnt[v], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
+// Inclusive sum (wave_incl_scan) and OR (wave_or, the whole wave's value in every lane) over the 64
+// lanes by DPP moves: row shifts inside the 16-lane rows, then the row broadcasts.  Each step is one
+// VALU instruction; a __shfl step is an LDS round trip (ds_bpermute), and a pass's scan was a chain
+// of six of them.  Every lane must be active.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return x;
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t x) {
+  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
+  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
+  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
 // In-place exclusive scan of a[0..N) in LDS by the whole workgroup; returns the total.
 // scratch needs THREADS/64 words.  Starts and ends with a workgroup barrier.
 template <int N, int THREADS>
@@ -123,12 +146,7 @@ __device__ __forceinline__ uint32_t lds_exclusive_scan(uint32_t* a, uint32_t* sc
     local[c] = idx < N ? a[idx] : 0u;
     sum += local[c];
   }
-  uint32_t x = sum;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
+  const uint32_t x = wave_incl_scan(sum);
   if (lane == 63) scratch[wid] = x;
   __syncthreads();
   uint32_t wpre = 0, total = 0;
@@ -152,8 +170,8 @@ __device__ __forceinline__ uint32_t lds_exclusive_scan(uint32_t* a, uint32_t* sc
 // Tile bucket offsets from per-wave bucket counts, with one block-wide scan.
 // On entry cnt[w*R + b] = number of keys of wave w in bucket b.  On exit cnt[w*R + b] = tile-local
 // start of wave w's run of bucket b, i.e. the exclusive prefix over (bucket, wave) in bucket-major
-// order, so runs of one bucket follow wave order (stable); lbase[b] = start of bucket b and
-// lbase[R] = number of keys in the tile.  scratch needs WAVES words.  Starts and ends with a
+// order, so runs of one bucket follow wave order (stable); with lbase, lbase[b] = start of bucket b
+// and lbase[R] = number of keys in the tile.  scratch needs WAVES words.  Starts and ends with a
 // workgroup barrier.
 template <int R, int WAVES>
 __device__ __forceinline__ void tile_bucket_offsets(uint32_t* cnt, uint32_t* lbase, uint32_t* scratch) {
@@ -168,12 +186,7 @@ __device__ __forceinline__ void tile_bucket_offsets(uint32_t* cnt, uint32_t* lba
     v[e] = f < N ? cnt[(f % WAVES) * R + f / WAVES] : 0u;
     sum += v[e];
   }
-  uint32_t x = sum;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
+  const uint32_t x = wave_incl_scan(sum);
   if (lane == 63) scratch[wid] = x;
   __syncthreads();
   uint32_t run = x - sum;
@@ -185,11 +198,11 @@ __device__ __forceinline__ void tile_bucket_offsets(uint32_t* cnt, uint32_t* lba
     if (f < N) {
       const int b = f / WAVES, w = f % WAVES;
       cnt[w * R + b] = run;
-      if (w == 0) lbase[b] = run;
+      if (lbase && w == 0) lbase[b] = run;
     }
     run += v[e];
   }
-  if (tid == THREADS - 1) lbase[R] = run;
+  if (lbase && tid == THREADS - 1) lbase[R] = run;
   __syncthreads();
 }
 

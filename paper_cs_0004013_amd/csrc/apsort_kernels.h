@@ -182,12 +182,7 @@ __global__ __launch_bounds__(THREADS) void k_hist_plan(
     __syncthreads();
     const uint32_t lane = tid & 63u, wid = tid >> 6;
     const uint32_t x0 = h[tid];
-    uint32_t x = x0;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t y = __shfl_up(x, off, 64);
-      if (lane >= (uint32_t)off) x += y;
-    }
+    const uint32_t x = wave_incl_scan(x0);
     if (lane == 63u) s_scan[wid] = x;
     __syncthreads();
     constexpr uint32_t WPD = R / 64;  // waves per digit

@@ -138,17 +138,18 @@ int seg_workgroups(const SegGroup& g, uint32_t nwork) {
 int seg_tile_keys(int cfg) { return kSegCfgs[cfg].waves * 64 * kSegCfgs[cfg].ipt; }
 
 // Single-array sort of n <= kSmallSortMax keys in one launch (one workgroup, keys in registers and
-// LDS): the smallest tile that holds them.  Up to 2048 keys 4 waves of 8 keys measured faster than
-// 16 waves of 2 (10.2-11.4 against 11.8-12.0 us); from 2049 to 4096 keys 16 waves of 4 took 13.0
-// against 16.0 us for the 8K-key tile.
-template <int BITS, int WAVES, int IPT>
+// LDS).  Few waves for few keys: a pass's scan and barriers grow with the waves, its rank and
+// reorder with the keys per lane.  Microseconds per launch, launches back to back (an empty kernel
+// takes 1.55): 1024 keys 3.9 with 4 waves, 5.2 with 8; 4096 keys 6.7 with 8, 7.7 with 4 or 16; 8192
+// keys 10.3 with 8, 11.1 with 16; 16384 keys 17.7 with 16.
+template <int WAVES, int IPT>
 static void launch_small(hipStream_t s, const uint32_t* in, uint32_t* out, uint32_t n, uint32_t P, uint32_t* spl) {
   if (lane_order_ok())
-    hipLaunchKernelGGL((k_sort_small<BITS, WAVES, IPT, seg_lcopies<BITS>(), SEG_RANK_ATOMIC>), dim3(1),
-                       dim3(WAVES * 64), 0, s, in, out, n, P, spl);
+    hipLaunchKernelGGL((k_sort_small<WAVES, IPT, SEG_RANK_ATOMIC>), dim3(1), dim3(WAVES * 64), 0, s, in, out, n, P,
+                       spl);
   else
-    hipLaunchKernelGGL((k_sort_small<BITS, WAVES, IPT, seg_lcopies<BITS>(), SEG_RANK_BALLOT>), dim3(1),
-                       dim3(WAVES * 64), 0, s, in, out, n, P, spl);
+    hipLaunchKernelGGL((k_sort_small<WAVES, IPT, SEG_RANK_BALLOT>), dim3(1), dim3(WAVES * 64), 0, s, in, out, n, P,
+                       spl);
 }
 
 ap_status enqueue_small_sort(const uint32_t* d_in, uint32_t* d_out, size_t n, int P, uint32_t* d_spl,
@@ -157,10 +158,9 @@ ap_status enqueue_small_sort(const uint32_t* d_in, uint32_t* d_out, size_t n, in
   const uint32_t nn = (uint32_t)n, PP = (uint32_t)P;
   uint32_t* spl = P > 1 ? d_spl : nullptr;
   prof_begin(AP_KIND_SEG, s);
-  if (n <= 2048) launch_small<8, 4, 8>(s, d_in, d_out, nn, PP, spl);
-  else if (n <= 4096) launch_small<8, 16, 4>(s, d_in, d_out, nn, PP, spl);
-  else if (n <= 8192) launch_small<8, 16, 8>(s, d_in, d_out, nn, PP, spl);
-  else launch_small<8, 16, 16>(s, d_in, d_out, nn, PP, spl);
+  if (n <= 2048) launch_small<4, 8>(s, d_in, d_out, nn, PP, spl);
+  else if (n <= 8192) launch_small<8, 16>(s, d_in, d_out, nn, PP, spl);
+  else launch_small<16, 16>(s, d_in, d_out, nn, PP, spl);
   prof_end(s);
   return check_launch(s, "k_sort_small");
 }

@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include "apsort.h"
+#include "apsort_block_sort.h"
 #include "apsort_device.h"
 #include "apsort_seg_types.h"
 
@@ -154,10 +155,13 @@ struct SegSmem {
     uint32_t hist[LCOPIES * (HW + 1)];
     struct P {
       uint32_t stage[T];
-      uint32_t cnt[WAVES * R];
+      // the tile sort of short segments counts 8-bit digits whatever BITS is
+      uint32_t cnt[WAVES * (R > kBlockRadix ? R : kBlockRadix)];
     } p;
   } u;
-  uint32_t base[HW];     // segment-wide exclusive bucket starts, per digit
+  // segment-wide exclusive bucket starts, per digit (tile sort of up to 4 waves: positions)
+  static constexpr int BASE = WAVES <= 4 && WAVES * kBlockRadix > HW ? WAVES * kBlockRadix : HW;
+  alignas(16) uint32_t base[BASE];
   uint32_t running[R];   // next free slot of each bucket in the current digit sweep
   uint32_t lbase[R + 1]; // tile-local bucket starts (+ tile size)
   uint32_t tot[R];       // tile bucket totals
@@ -183,12 +187,7 @@ __device__ __forceinline__ void seg_splitters(const SegDesc& dsc, uint32_t len) 
 
 // Tile rank of the keys k[] (wave-striped order) by the digit at `shift`: per-wave LDS counters,
 // then one scan gives cnt[w][v] = tile-local start of wave w's run of bucket v, lbase (bucket
-// starts) and tot (bucket totals).  SEG_RANK_ATOMIC ranks with lane-ordered LDS atomics
-// (rank_slot), which the host selects only on a device that passed the lane-order check;
-// SEG_RANK_BALLOT ranks with one ballot per digit bit (rank_ballot) and needs no ordering
-// property of the LDS.
-enum SegRank : int { SEG_RANK_ATOMIC = 0, SEG_RANK_BALLOT = 1 };
-
+// starts) and tot (bucket totals).  RANK: SegRank.
 template <int BITS, int WAVES, int IPT, int LCOPIES, int RANK>
 __device__ __forceinline__ void seg_rank_tile(SegSmem<BITS, WAVES, IPT, LCOPIES>& sm, const uint32_t (&k)[IPT],
                                               uint32_t (&r)[IPT], int shift) {
@@ -209,60 +208,47 @@ __device__ __forceinline__ void seg_rank_tile(SegSmem<BITS, WAVES, IPT, LCOPIES>
   __syncthreads();
 }
 
-// A segment of len <= T keys sorted by the workgroup entirely in registers and LDS: per digit a
-// rank, a constant-digit test and a reorder through LDS; one read and one write of every key
-// (src == dst allowed: every key is in registers before the first write).  Then the splitters.
-template <int BITS, int WAVES, int IPT, int LCOPIES, int RANK>
+// A segment of len <= WAVES * 64 * IPT keys sorted by the workgroup entirely in registers and LDS
+// (block_sort): one read and one write of every key (src == dst allowed: every key is in registers
+// before the first write), then the splitters.  The tile is taken with the fewest keys per lane
+// that hold the segment, in steps of a factor of two: the time of a tile follows its keys per lane,
+// not the segment's length.
+template <int BITS, int WAVES, int IPT, int LCOPIES, int RANK, int I = IPT>
 __device__ __forceinline__ void seg_sort_one_tile(SegSmem<BITS, WAVES, IPT, LCOPIES>& sm, const SegDesc& dsc,
                                                   uint32_t len) {
-  using SM = SegSmem<BITS, WAVES, IPT, LCOPIES>;
-  constexpr int R = SM::R, D = SM::D, T = SM::T, THREADS = WAVES * 64;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  uint32_t k[IPT], r[IPT];
-  const uint32_t lb0 = (uint32_t)(wid * 64 * IPT + lane);
+  if constexpr (I > 1) {
+    if (len <= (uint32_t)(WAVES * 64 * (I / 2))) {
+      seg_sort_one_tile<BITS, WAVES, IPT, LCOPIES, RANK, I / 2>(sm, dsc, len);
+      return;
+    }
+  }
   const gptr<const uint32_t> in = gmem(dsc.src);
   const gptr<uint32_t> out = gmem(dsc.dst);
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const uint32_t idx = lb0 + j * 64;
-    k[j] = idx < len ? in[idx] : 0xFFFFFFFFu;
-  }
-  const uint32_t nsent = (uint32_t)T - len;
-#pragma unroll 1
-  for (int d = 0; d < D; ++d) {
-    const int shift = d * BITS;
-    seg_rank_tile<BITS, WAVES, IPT, LCOPIES, RANK>(sm, k, r, shift);
-    // constant digit over the segment's keys (sentinels sit in the largest bucket)
-    if (tid == 0) sm.flag[0] = 0u;
-    __syncthreads();
-    const uint32_t vmax = (0xFFFFFFFFu >> shift) & (R - 1);
-    for (int b = tid; b < R; b += THREADS)
-      if (sm.tot[b] - ((uint32_t)b == vmax ? nsent : 0u) == len) sm.flag[0] = 1u;
-    __syncthreads();
-    if (sm.flag[0]) continue;  // uniform across the workgroup
-    uint32_t* cnt = sm.u.p.cnt + wid * R;
-#pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-      const uint32_t v = (k[j] >> shift) & (R - 1);
-      sm.u.p.stage[cnt[v] + r[j]] = k[j];
+  const BlockSortLds lds{sm.u.p.stage, sm.u.p.cnt, sm.base, sm.scan};
+  uint32_t k[I];
+  block_load<WAVES, I>(in, len, k);
+  const uint32_t first = len ? in[0] : 0u;
+  const uint32_t diff = varying_bits<WAVES, I>(k, first, len, sm.scan);
+  block_sort<WAVES, I, RANK>(lds, k, diff);
+  block_store<WAVES, I>(out, len, k);
+  if (dsc.spl) {
+    // From LDS: the last digit pass left the sorted tile in the stage (with no pass every key is
+    // the first one).  Reading them back from memory waits for the stores above and then for the
+    // loads (0.1-0.2 us of a sort of 2K keys and more).
+    const uint32_t P = dsc.P, q = len / P, r = len % P;
+    const gptr<uint32_t> spl = gmem(dsc.spl);
+    for (uint32_t p = threadIdx.x + 1; p < P; p += WAVES * 64) {
+      const uint64_t start = (uint64_t)p * q + (p < r ? p : r);
+      spl[p - 1] = start < len ? (diff ? lds.stage[start] : first) : 0xFFFFFFFFu;
     }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < IPT; ++j) k[j] = sm.u.p.stage[lb0 + j * 64];
   }
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const uint32_t idx = lb0 + j * 64;
-    if (idx < len) out[idx] = k[j];
-  }
-  seg_splitters<THREADS>(dsc, len);
 }
 
 // The single-array sort of a short array (n <= T) in one launch: one workgroup, seg_sort_one_tile.
-template <int BITS, int WAVES, int IPT, int LCOPIES, int RANK>
+template <int WAVES, int IPT, int RANK>
 __global__ __launch_bounds__(WAVES * 64) void k_sort_small(const uint32_t* src, uint32_t* dst, uint32_t n, uint32_t P,
                                                           uint32_t* spl) {
-  __shared__ SegSmem<BITS, WAVES, IPT, LCOPIES> sm;
+  __shared__ __align__(16) SegSmem<kBlockBits, WAVES, IPT, 1> sm;
   SegDesc dsc;
   dsc.src = src;
   dsc.dst = dst;
@@ -271,7 +257,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_sort_small(const uint32_t* src, 
   dsc.n = n;
   dsc.P = P;
   dsc.pad[0] = dsc.pad[1] = 0u;
-  seg_sort_one_tile<BITS, WAVES, IPT, LCOPIES, RANK>(sm, dsc, n);
+  seg_sort_one_tile<kBlockBits, WAVES, IPT, 1, RANK>(sm, dsc, n);
 }
 
 // Persistent segmented sort over the descriptors order[lo..hi), longest first.  With
@@ -285,7 +271,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_seg_sort(const SegDesc* __restri
   using SM = SegSmem<BITS, WAVES, IPT, LCOPIES>;
   constexpr int R = SM::R, D = SM::D, T = SM::T, HW = SM::HW, THREADS = WAVES * 64;
   constexpr int CS = HW + 1;
-  __shared__ SM sm;
+  __shared__ __align__(16) SM sm;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   uint32_t lo = item_lo, hi = item_hi;
   if (item_hi == ~0u) {

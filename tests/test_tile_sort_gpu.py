@@ -1,0 +1,48 @@
+"""The sort of one tile in registers and LDS (short arrays and segments) at the edges of its
+keys-per-lane steps, on keys whose varying bits start and end anywhere."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import announce, gpu_sort, to_dev, to_host, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+# workgroups of 4, 8 and 16 waves step at 256, 512 and 1024 keys times a power of two
+EDGES = [1, 2, 64, 255, 256, 257, 512, 513, 1025, 2047, 2048, 2049, 4096, 4097, 8191, 8193, 16383, 16384]
+
+
+def _keys(n: int, kind: str) -> np.ndarray:
+    full = np.random.default_rng(n).integers(0, 1 << 32, size=n, dtype=np.uint64).astype(np.uint32)
+    return {"full": full,
+            "top_bit": full & np.uint32(0x80000000),
+            "one_window": (full & np.uint32(0x0001FE00)) | np.uint32(0xA00000F1),
+            "split_windows": (full & np.uint32(0xC0000003)) | np.uint32(0x00FFFF00),
+            "equal": np.full(n, 0xFFFFFFFF, np.uint32)}[kind]
+
+
+@pytest.mark.parametrize("rank_mode", [0, 1])
+@pytest.mark.parametrize("kind", ["full", "top_bit", "one_window", "split_windows", "equal"])
+def test_tile_edges(kind, rank_mode):
+    torch = torch_cuda()
+    from paper_cs_0004013_amd import binding
+    binding.ap_set_rank_mode(rank_mode)
+    try:
+        for n in EDGES:
+            keys = _keys(n, kind)
+            announce(f"tile sort n={n} {kind} rank {rank_mode}")
+            out, spl = gpu_sort(keys, 64)
+            want = oracle.sort_u32(keys)
+            assert np.array_equal(out, want), n
+            assert np.array_equal(spl, oracle.splitters(want, 64)), n
+        # the same lengths as segments of one batch
+        keys = np.concatenate([_keys(n, kind) for n in EDGES])
+        off = np.concatenate([[0], np.cumsum(EDGES)]).astype(np.uint32)
+        t, _ = to_dev(keys)
+        binding.ap_sort_u32_segmented(t, torch.from_numpy(off.view(np.int32)).to("cuda"))
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(t), oracle.sort_segmented(keys, off.astype(np.uint64)))
+    finally:
+        binding.ap_set_rank_mode(0)
