@@ -72,11 +72,13 @@ typedef enum {
  * Digit columns whose value is the same for every key are not sorted on (the
  * pass is an identity); this is decided on the device, with no host sync.
  * Arrays of at most 16384 keys are sorted in one launch by one workgroup in
- * registers and LDS, with no scratch memory.  Longer ones take the
- * device-wide passes.  Their scratch memory (about 4n bytes plus the scan state)
+ * registers and LDS, with no scratch memory.  Arrays of up to 9 * 2^17 keys
+ * are split into cells of neighbouring keys (at splitters drawn from a sample)
+ * and every cell is sorted by one workgroup, two launches; longer ones take
+ * the device-wide digit passes.  Their scratch memory (about 4n bytes plus the scan state)
  * comes from a per-device, per-stream cache that grows on demand; growing
  * synchronises `stream` first.  Use ap_sort_u32_ws to bring your own
- * workspace instead (it always takes the device-wide passes).
+ * workspace instead.
  */
 ap_status ap_sort_u32(const uint32_t *d_in, uint32_t *d_out, size_t n, int P,
                       uint32_t *d_splitters, void *stream);
@@ -428,8 +430,9 @@ ap_status ap_release_cache(void);
  * events, adds each launch's duration to its kind, returns the totals and
  * clears them.  Kinds: AP_KIND_HIST (bucket counts + plan), AP_KIND_PASS + d
  * (digit pass d, d = 0..7; a pass the plan skips still records its near-empty
- * launch), AP_KIND_FINAL (copy + splitters), AP_KIND_MERGE (ap_merge_*), AP_KIND_SEG (segmented-sort
- * kernels).  ms and launches have at least AP_NKINDS entries.
+ * launch; of the two-launch sort of middling arrays the split is pass 0 and the cell sort pass 1),
+ * AP_KIND_FINAL (copy + splitters), AP_KIND_MERGE (ap_merge_*), AP_KIND_SEG (segmented-sort kernels
+ * and sorts of one launch).  ms and launches have at least AP_NKINDS entries.
  */
 enum { AP_KIND_HIST = 0, AP_KIND_PASS = 1, AP_KIND_FINAL = 9, AP_KIND_SEG = 10, AP_KIND_MERGE = 11, AP_NKINDS = 16 };
 ap_status ap_profile_enable(int on);

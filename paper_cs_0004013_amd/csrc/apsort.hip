@@ -211,7 +211,10 @@ Layout layout_for(size_t n, bool pairs) {
   L.plan = off;   off += align_up(sizeof(uint32_t) * PL_WORDS, 256);
   L.done = off;   off += 256;
   L.tctr = off;   off += 256;
-  L.status = off; off += align_up(sizeof(uint32_t) * (size_t)kDigits * L.ntiles * kRadix, 256);
+  // the two-launch sort keeps its splitters and table where the digit passes keep their status words
+  L.status = off;
+  off += std::max(align_up(sizeof(uint32_t) * (size_t)kDigits * L.ntiles * kRadix, 256),
+                  cells_sort_size(n, pairs) ? cells_table_bytes(n, pairs) : (size_t)0);
   L.zero_bytes = off - L.tctr;  // upper bound of the region k_hist_plan clears
   L.tmp = off;    off += align_up(sizeof(uint32_t) * n, 256);
   L.vtmp = off;
@@ -347,6 +350,15 @@ ap_status enqueue_sort_parts(const uint32_t* d_in, uint32_t* d_out, size_t n, in
   const int cus = device_cus();
   const int inplace = (d_in == d_out) ? 1 : 0;
   const bool atomic_rank = lane_order_ok();
+  const PassDebugState dbg = pass_debug();
+  // Short arrays take one workgroup, middling ones the two-launch sort, unless the digit passes are
+  // asked for (a forced tile shape, a debug mode of the pass, the bucketing variant's digits).
+  if (first_digit == 0 && g_shape_override.load() < 0 && dbg.mode == PASS_DBG_NONE) {
+    if (small_sort_size(n, pairs))
+      return pairs ? enqueue_pairs_small(d_in, d_vin, d_out, d_vout, n, P, d_spl, s)
+                   : enqueue_small_sort(d_in, d_out, n, P, d_spl, s);
+    if (cells_sort_size(n, pairs)) return enqueue_cells(d_in, d_out, d_vin, d_vout, n, P, d_spl, status, tmp, vtmp, s);
+  }
   const int sh = pairs ? std::min(shape_for_pairs(n), shape_used(n, atomic_rank)) : shape_used(n, atomic_rank);
   const int T = tile_keys(sh);
   const uint32_t ntiles = (uint32_t)((n + T - 1) / T);
@@ -366,7 +378,6 @@ ap_status enqueue_sort_parts(const uint32_t* d_in, uint32_t* d_out, size_t n, in
     if (st != AP_OK) return st;
   }
   // A3-A6: one launch per digit; passes the plan skips exit at once
-  const PassDebugState dbg = pass_debug();
   for (int d = 0; d < kDigits; ++d) {
     uint32_t* st_d = status + (size_t)d * ntiles * kRadix;
     const uint32_t* base_d = base + d * kRadix;
@@ -652,8 +663,8 @@ ap_status ap_sort_u32(const uint32_t* d_in, uint32_t* d_out, size_t n, int P, ui
   if (st != AP_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (n == 0) return sort_with_ws(d_in, d_out, 0, P, d_splitters, nullptr, 0, s);
-  // A short array is sorted in one launch by one workgroup (unless a pass shape is forced, which
-  // pins the device-wide kernels at every size).
+  // A short array is sorted in one launch by one workgroup and needs no workspace (unless a pass
+  // shape is forced, which pins the device-wide kernels at every size).
   if (n <= kSmallSortMax && g_shape_override.load() < 0) {
     st = check_lane_order(s);
     if (st != AP_OK) return st;

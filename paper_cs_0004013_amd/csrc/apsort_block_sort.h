@@ -28,13 +28,14 @@ enum SegRank : int { SEG_RANK_ATOMIC = 0, SEG_RANK_BALLOT = 1 };
 constexpr int kBlockBits = 8;
 constexpr int kBlockRadix = 1 << kBlockBits;
 
-// LDS of block_sort.  stage: WAVES*64*IPT words; cnt: WAVES*256; off: WAVES*256 (WAVES <= 4 only);
-// scan: WAVES words.
+// LDS of block_sort.  stage: WAVES*64*IPT words (vstage the same, with values); cnt: WAVES*256; off:
+// WAVES*256 (WAVES <= 4 only); scan: WAVES words.
 struct BlockSortLds {
   uint32_t* stage;
   uint32_t* cnt;
   uint32_t* off;
   uint32_t* scan;
+  uint32_t* vstage;
 };
 
 // A tile of len <= WAVES * 64 * IPT keys between memory and registers; the registers behind the
@@ -73,10 +74,13 @@ __device__ __forceinline__ uint32_t varying_bits(const uint32_t (&k)[IPT], uint3
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 
-// Sorts the tile in k[] on the bits set in diff (bits outside it must be equal in all its keys): on
-// return k[] holds the sorted tile, laid out the same way.
-template <int WAVES, int IPT, int RANK>
-__device__ __forceinline__ void block_sort(const BlockSortLds& sm, uint32_t (&k)[IPT], uint32_t diff) {
+// Sorts the tile in k[] (sentinels all-ones behind the keys) on the bits set in diff: on return k[]
+// holds the sorted tile in the same striped order, and so does the stage if diff was not zero.  Bits
+// outside diff must be equal in all keys.  KV: the values in v[] move with their keys, equal keys
+// keeping their order.
+template <int WAVES, int IPT, int RANK, bool KV>
+__device__ __forceinline__ void block_sort_impl(const BlockSortLds& sm, uint32_t (&k)[IPT], uint32_t* v,
+                                                uint32_t diff) {
   constexpr int R = kBlockRadix;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const uint32_t lb0 = (uint32_t)(wid * 64 * IPT + lane);
@@ -92,9 +96,9 @@ __device__ __forceinline__ void block_sort(const BlockSortLds& sm, uint32_t (&k)
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
-      const uint32_t v = (k[j] >> shift) & (R - 1);
-      if constexpr (RANK == SEG_RANK_ATOMIC) r[j] = rank_slot(cnt, v);
-      else r[j] = rank_ballot<kBlockBits>(cnt, v);
+      const uint32_t b = (k[j] >> shift) & (R - 1);
+      if constexpr (RANK == SEG_RANK_ATOMIC) r[j] = rank_slot(cnt, b);
+      else r[j] = rank_ballot<kBlockBits>(cnt, b);
     }
     if constexpr (WAVES <= 4) {
       // lane l of every wave takes buckets 4l .. 4l+3: their totals over the waves, their keys in
@@ -117,12 +121,24 @@ __device__ __forceinline__ void block_sort(const BlockSortLds& sm, uint32_t (&k)
       tile_bucket_offsets<R, WAVES>(sm.cnt, nullptr, sm.scan);
     }
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) sm.stage[off[(k[j] >> shift) & (R - 1)] + r[j]] = k[j];
+    for (int j = 0; j < IPT; ++j) {
+      const uint32_t p = off[(k[j] >> shift) & (R - 1)] + r[j];
+      sm.stage[p] = k[j];
+      if constexpr (KV) sm.vstage[p] = v[j];
+    }
     if constexpr (WAVES > 1) __syncthreads();
     else __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) k[j] = sm.stage[lb0 + j * 64u];
+    for (int j = 0; j < IPT; ++j) {
+      k[j] = sm.stage[lb0 + j * 64u];
+      if constexpr (KV) v[j] = sm.vstage[lb0 + j * 64u];
+    }
   }
+}
+
+template <int WAVES, int IPT, int RANK>
+__device__ __forceinline__ void block_sort(const BlockSortLds& sm, uint32_t (&k)[IPT], uint32_t diff) {
+  block_sort_impl<WAVES, IPT, RANK, false>(sm, k, nullptr, diff);
 }
 
 }  // namespace aps

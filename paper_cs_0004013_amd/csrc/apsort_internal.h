@@ -76,6 +76,15 @@ ap_status cached_workspace(size_t need, hipStream_t s, void** out);
 constexpr uint32_t kSmallSortMax = 16384;
 ap_status enqueue_small_sort(const uint32_t* d_in, uint32_t* d_out, size_t n, int P, uint32_t* d_spl,
                              hipStream_t s);
+// Arrays sorted in two launches, split into cells and cell sort (apsort_cells.hip).  tables:
+// cells_table_bytes of scratch, tmp (and vtmp with values) n words.
+bool small_sort_size(size_t n, bool pairs);
+bool cells_sort_size(size_t n, bool pairs);
+size_t cells_table_bytes(size_t n, bool pairs);
+ap_status enqueue_cells(const uint32_t* in, uint32_t* out, const uint32_t* vin, uint32_t* vout, size_t n, int P,
+                        uint32_t* d_spl, void* tables, uint32_t* tmp, uint32_t* vtmp, hipStream_t s);
+ap_status enqueue_pairs_small(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, size_t n, int P,
+                              uint32_t* d_spl, hipStream_t s);
 // k_finalize alone: copy the plan's final buffer into d_out if the plan says so, and the splitters.
 ap_status enqueue_finalize(const uint32_t* d_in, uint32_t* d_out, const uint32_t* tmp, size_t n, const uint32_t* plan,
                            int P, uint32_t* d_spl, hipStream_t s);

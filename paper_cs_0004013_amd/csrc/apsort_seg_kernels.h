@@ -224,7 +224,7 @@ __device__ __forceinline__ void seg_sort_one_tile(SegSmem<BITS, WAVES, IPT, LCOP
   }
   const gptr<const uint32_t> in = gmem(dsc.src);
   const gptr<uint32_t> out = gmem(dsc.dst);
-  const BlockSortLds lds{sm.u.p.stage, sm.u.p.cnt, sm.base, sm.scan};
+  const BlockSortLds lds{sm.u.p.stage, sm.u.p.cnt, sm.base, sm.scan, nullptr};
   uint32_t k[I];
   block_load<WAVES, I>(in, len, k);
   const uint32_t first = len ? in[0] : 0u;
