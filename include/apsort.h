@@ -240,11 +240,12 @@ ap_status ap_digit_plan_u32(const uint32_t *d_in, size_t n, int digit_bits,
  *              completes with the stream work rather than at the call.
  *
  * Segments shorter than the long-segment threshold (ap_segmented_set_long_min,
- * default 2^20 keys) are sorted by one workgroup each: segments that fit one
- * tile in registers and LDS (one read and one write of each key); longer ones
- * by the same workgroup with a histogram sweep and one sweep per non-constant
- * digit; they are scheduled longest first by persistent kernels, one per
- * length group.  Segments at or above the threshold are sorted like one
+ * default 2^20 keys) are sorted by one wave (up to 1024 keys) or one workgroup
+ * each: segments that fit one tile in registers and LDS (one read and one
+ * write of each key); longer ones by the same workgroup with a histogram sweep
+ * and one sweep per non-constant digit.  Segments of up to 4096 keys are taken
+ * in the order of the offsets, longer ones longest first by persistent
+ * kernels, one per length group.  Segments at or above the threshold are sorted like one
  * array, by device-wide digit passes (bucket counts per segment, then one pass
  * per non-constant digit with a single-pass scan over the tiles of all long
  * segments), beside the workgroup-per-segment kernels.  No host

@@ -29,7 +29,7 @@ constexpr int kBlockBits = 8;
 constexpr int kBlockRadix = 1 << kBlockBits;
 
 // LDS of block_sort.  stage: WAVES*64*IPT words (vstage the same, with values); cnt: WAVES*256; off:
-// WAVES*256 (WAVES <= 4 only); scan: WAVES words.
+// WAVES*256 (2 to 4 waves only); scan: WAVES words.
 struct BlockSortLds {
   uint32_t* stage;
   uint32_t* cnt;
@@ -38,18 +38,27 @@ struct BlockSortLds {
   uint32_t* vstage;
 };
 
+// Index of thread tid's first key in the tile.  With one wave the tile belongs to the wave, whatever
+// its place in the workgroup.  (tid: threadIdx.x, in a loop over tiles fresh_tid().)
+template <int WAVES, int IPT>
+__device__ __forceinline__ uint32_t block_first(uint32_t tid) {
+  return WAVES == 1 ? tid & 63u : (tid >> 6) * (64u * IPT) + (tid & 63u);
+}
+
 // A tile of len <= WAVES * 64 * IPT keys between memory and registers; the registers behind the
 // last key get all-ones sentinels, which sort behind every key.
 template <int WAVES, int IPT>
-__device__ __forceinline__ void block_load(gptr<const uint32_t> in, uint32_t len, uint32_t (&k)[IPT]) {
-  const uint32_t lb0 = (threadIdx.x >> 6) * (64u * IPT) + (threadIdx.x & 63u);
+__device__ __forceinline__ void block_load(gptr<const uint32_t> in, uint32_t len, uint32_t (&k)[IPT],
+                                           uint32_t tid = threadIdx.x) {
+  const uint32_t lb0 = block_first<WAVES, IPT>(tid);
 #pragma unroll
   for (int j = 0; j < IPT; ++j) k[j] = lb0 + j * 64u < len ? in[lb0 + j * 64u] : 0xFFFFFFFFu;
 }
 
 template <int WAVES, int IPT>
-__device__ __forceinline__ void block_store(gptr<uint32_t> out, uint32_t len, const uint32_t (&k)[IPT]) {
-  const uint32_t lb0 = (threadIdx.x >> 6) * (64u * IPT) + (threadIdx.x & 63u);
+__device__ __forceinline__ void block_store(gptr<uint32_t> out, uint32_t len, const uint32_t (&k)[IPT],
+                                            uint32_t tid = threadIdx.x) {
+  const uint32_t lb0 = block_first<WAVES, IPT>(tid);
 #pragma unroll
   for (int j = 0; j < IPT; ++j)
     if (lb0 + j * 64u < len) out[lb0 + j * 64u] = k[j];
@@ -59,14 +68,14 @@ __device__ __forceinline__ void block_store(gptr<uint32_t> out, uint32_t len, co
 // scratch: WAVES words.  Contains one barrier (none with one wave).
 template <int WAVES, int IPT>
 __device__ __forceinline__ uint32_t varying_bits(const uint32_t (&k)[IPT], uint32_t first, uint32_t len,
-                                                 uint32_t* scratch) {
-  const uint32_t lb0 = (threadIdx.x >> 6) * (64u * IPT) + (threadIdx.x & 63u);
+                                                 uint32_t* scratch, uint32_t tid = threadIdx.x) {
+  const uint32_t lb0 = block_first<WAVES, IPT>(tid);
   uint32_t x = 0u;
 #pragma unroll
   for (int j = 0; j < IPT; ++j) x |= lb0 + j * 64u < len ? (k[j] ^ first) : 0u;
   x = wave_or(x);
   if constexpr (WAVES == 1) return x;
-  if ((threadIdx.x & 63u) == 0u) scratch[threadIdx.x >> 6] = x;
+  if ((tid & 63u) == 0u) scratch[tid >> 6] = x;
   __syncthreads();
   x = 0u;
 #pragma unroll
@@ -80,12 +89,12 @@ __device__ __forceinline__ uint32_t varying_bits(const uint32_t (&k)[IPT], uint3
 // keeping their order.
 template <int WAVES, int IPT, int RANK, bool KV>
 __device__ __forceinline__ void block_sort_impl(const BlockSortLds& sm, uint32_t (&k)[IPT], uint32_t* v,
-                                                uint32_t diff) {
+                                                uint32_t diff, uint32_t tid = threadIdx.x) {
   constexpr int R = kBlockRadix;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const uint32_t lb0 = (uint32_t)(wid * 64 * IPT + lane);
+  const int lane = (int)(tid & 63u), wid = WAVES == 1 ? 0 : (int)(tid >> 6);
+  const uint32_t lb0 = block_first<WAVES, IPT>(tid);
   uint32_t* const cnt = sm.cnt + wid * R;
-  uint32_t* const off = WAVES <= 4 ? sm.off + wid * R : cnt;
+  uint32_t* const off = WAVES > 1 && WAVES <= 4 ? sm.off + wid * R : cnt;
   uint4* const cnt4 = reinterpret_cast<uint4*>(cnt);
   uint32_t r[IPT];
 #pragma unroll 1
@@ -118,7 +127,7 @@ __device__ __forceinline__ void block_sort_impl(const BlockSortLds& sm, uint32_t
       reinterpret_cast<uint4*>(off)[lane] = make_uint4(b0 + low.x, b1 + low.y, b2 + low.z, b3 + low.w);
       __builtin_amdgcn_wave_barrier();
     } else {
-      tile_bucket_offsets<R, WAVES>(sm.cnt, nullptr, sm.scan);
+      tile_bucket_offsets<R, WAVES>(sm.cnt, nullptr, sm.scan, (int)tid);
     }
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
@@ -137,8 +146,9 @@ __device__ __forceinline__ void block_sort_impl(const BlockSortLds& sm, uint32_t
 }
 
 template <int WAVES, int IPT, int RANK>
-__device__ __forceinline__ void block_sort(const BlockSortLds& sm, uint32_t (&k)[IPT], uint32_t diff) {
-  block_sort_impl<WAVES, IPT, RANK, false>(sm, k, nullptr, diff);
+__device__ __forceinline__ void block_sort(const BlockSortLds& sm, uint32_t (&k)[IPT], uint32_t diff,
+                                           uint32_t tid = threadIdx.x) {
+  block_sort_impl<WAVES, IPT, RANK, false>(sm, k, nullptr, diff, tid);
 }
 
 }  // namespace aps

@@ -483,7 +483,7 @@ constexpr uint32_t kCellShareRun = 32;
 constexpr uint32_t kMaxCells = 512;
 
 template <int WAVES, int IPT, int RANK, bool KV>
-__global__ __launch_bounds__(WAVES * 64) void k_cells(SplitArray a, uint32_t* __restrict__ out, uint32_t* __restrict__ vout,
+__global__ __launch_bounds__(WAVES * 64, 4) void k_cells(SplitArray a, uint32_t* __restrict__ out, uint32_t* __restrict__ vout,
                                                      const uint32_t* __restrict__ spl, uint32_t P,
                                                      uint32_t* __restrict__ cell_splitters) {
   constexpr uint32_t THREADS = WAVES * 64, CAP = THREADS * IPT;

@@ -39,6 +39,11 @@ __device__ __forceinline__ unsigned long long ld_agent_u64(const unsigned long l
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Waits until this thread's stores and atomics have been performed where the whole device sees them
+// (agent-scope atomics are performed at the memory side).  Before a counter that tells another
+// workgroup so.  A device-scope release fence would do it too, but also writes back the L2.
+__device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Global-memory view of a pointer.  A pointer that a kernel reads from memory (a descriptor field)
 // is generic to the compiler, which then accesses it with flat instructions.  A flat access counts
 // against the LDS wait counter as well as the vector-memory one, so every LDS wait of a rank or a
@@ -49,6 +54,14 @@ using gptr = __attribute__((address_space(1))) T*;
 template <class T>
 __device__ __forceinline__ gptr<T> gmem(T* p) {
   return (gptr<T>)p;
+}
+
+// The thread index as a value of its own: inside a loop over work items, addresses made from it are
+// not hoisted out of the loop and kept in registers for every item (and every tile size).
+__device__ __forceinline__ uint32_t fresh_tid() {
+  uint32_t t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
 }
 
 // Number of set bits of m in lanes below the calling lane.
@@ -174,9 +187,10 @@ __device__ __forceinline__ uint32_t lds_exclusive_scan(uint32_t* a, uint32_t* sc
 // and lbase[R] = number of keys in the tile.  scratch needs WAVES words.  Starts and ends with a
 // workgroup barrier.
 template <int R, int WAVES>
-__device__ __forceinline__ void tile_bucket_offsets(uint32_t* cnt, uint32_t* lbase, uint32_t* scratch) {
+__device__ __forceinline__ void tile_bucket_offsets(uint32_t* cnt, uint32_t* lbase, uint32_t* scratch,
+                                                    int tid = (int)threadIdx.x) {
   constexpr int THREADS = WAVES * 64, N = R * WAVES, E = (N + THREADS - 1) / THREADS;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int lane = tid & 63, wid = tid >> 6;
   __syncthreads();
   uint32_t v[E];
   uint32_t sum = 0u;

@@ -58,7 +58,6 @@ bool seg_group_one_tile(const SegGroup& g);
 int seg_tile_keys(int cfg);
 void seg_groups(SegGroup* out);  // kSegGroups entries
 ap_status seg_groups_check(const SegGroup* grp);  // the used groups partition classes 1..31
-void seg_reset(hipStream_t s, SegCtl* ctl);
 // d_vout != nullptr: (key, value) pairs, the values read from d_vin and written to d_vout
 // (workspace from layout_for(n, true)).
 // first_digit > 0: only digits first_digit.. are sorted on (the bucketing variant's high-order

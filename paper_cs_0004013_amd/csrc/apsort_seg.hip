@@ -165,8 +165,6 @@ ap_status enqueue_small_sort(const uint32_t* d_in, uint32_t* d_out, size_t n, in
   return check_launch(s, "k_sort_small");
 }
 
-void seg_reset(hipStream_t s, SegCtl* ctl) { hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, s, ctl); }
-
 // Length groups: group g sorts the segments whose length class ceil(log2(length)) lies in
 // [cls_lo, cls_hi] with kernel configuration cfg.  The defaults give each tile size its own
 // classes: up to 2K keys with 2K-key tiles, (2K, 4K] with 4K-key tiles, (4K, 8K] with 8K-key
@@ -322,14 +320,17 @@ static ap_status seg_entry(hipStream_t s, size_t need, SegEntry** out, bool* fre
 
 // A fresh workspace: zero the control block (offset 0 whatever the sizes; every call leaves it
 // zero again).  Everything else is written by each call before it is read: the long segments'
-// bucket counts, whose place depends on the call's sizes, are zeroed by k_seg_fill.
+// bucket counts, whose place depends on the call's sizes, are zeroed by k_seg_tiles.
 static ap_status seg_zero_fresh(void* ws, const SegLayout& L, hipStream_t s) {
   char* w = static_cast<char*>(ws);
   return fill_u32(reinterpret_cast<uint32_t*>(w + L.ctl), 0u, up256(sizeof(SegCtl)) / 4, s);
 }
 
-// The launch sequence: classify -> fill -> persistent sort.  No host synchronisation; every grid
-// size is fixed by (nseg, device), so the sequence can be captured once and replayed.
+// The launch sequence: classify -> tiles -> groups and long segments side by side -> finish.  No host
+// synchronisation; every grid size is fixed by (nseg, device), so the sequence can be captured once
+// and replayed.  Launches and the events between streams are what a batch of short segments spends
+// its time on, so nothing is launched that cannot have work: the groups of lengths that k_seg_tiles
+// sorts, and the long segments' kernels when no segment can be that long.
 ap_status enqueue_segmented(uint32_t* d_keys, size_t n_total, const uint32_t* d_off, int nseg, uint32_t* d_status,
                             void* ws, const SegLayout& L, int cfg, hipStream_t s, const hipStream_t* aux,
                             hipEvent_t ev_fork, const hipEvent_t* ev_join) {
@@ -348,41 +349,57 @@ ap_status enqueue_segmented(uint32_t* d_keys, size_t n_total, const uint32_t* d_
   prof_begin(AP_KIND_SEG, s);
   hipLaunchKernelGGL(k_seg_classify, dim3(g1), dim3(256), 0, s, d_off, (uint32_t)nseg, (uint32_t)n_total,
                      L.long_min, ctl, d_status);
-  hipLaunchKernelGGL(k_seg_fill, dim3(g1), dim3(256), 0, s, d_off, (uint32_t)nseg, (uint32_t)n_total, L.long_min,
-                     long_tile, ctl, d_keys, tmp, order, longs, lhist);
+  // 24 or more workgroups per CU where there are segments enough: their lengths, and so their times,
+  // differ, and the device evens them out
+  const uint32_t chunk = (uint32_t)std::min(64, std::max(1, nseg / (24 * cus)));
+  const dim3 gt(((uint32_t)nseg + chunk - 1) / chunk);
+  if (atomic_rank)
+    hipLaunchKernelGGL((k_seg_tiles<SEG_RANK_ATOMIC>), gt, dim3(256), 0, s, d_off, (uint32_t)nseg, chunk, L.long_min,
+                       long_tile, ctl, d_keys, tmp, order, longs, lhist);
+  else
+    hipLaunchKernelGGL((k_seg_tiles<SEG_RANK_BALLOT>), gt, dim3(256), 0, s, d_off, (uint32_t)nseg, chunk, L.long_min,
+                       long_tile, ctl, d_keys, tmp, order, longs, lhist);
   // One persistent kernel per length group.  The groups sort disjoint segments and take work from
   // counters of their own, so they run concurrently: the first group (longest segments) on `s`,
-  // the others on auxiliary streams forked after k_seg_fill and joined before the reset.  A
+  // the others on auxiliary streams forked after k_seg_tiles and joined before the finish.  A
   // group's workgroups then fill the CUs that another group's tail (its few longest segments)
   // leaves idle, instead of waiting for that kernel to end.
   SegGroup grp[kSegGroups];
   seg_groups(grp);
-  hipError_t e = hipEventRecord(ev_fork, s);
-  if (e != hipSuccess) return hip_fail(e, "hipEventRecord(fork)");
-  bool first = true;
-  for (int g = 0; g < kSegGroups; ++g) {
-    if (grp[g].cls_lo > grp[g].cls_hi) continue;
-    const dim3 grid(seg_workgroups(grp[g], (uint32_t)nseg));
-    if (first) {
-      launch_seg_group(grp[g], grid, s, order, 0u, ~0u, g, ctl);
+  hipError_t e = hipSuccess;
+  const bool any = n_total > kSegTileMax;  // some segment may be too long for k_seg_tiles
+  bool first = true, forked = false;
+  auto fork = [&](hipStream_t side) {
+    if (!forked) e = hipEventRecord(ev_fork, s);
+    forked = true;
+    if (e == hipSuccess) e = hipStreamWaitEvent(side, ev_fork, 0);
+    return e;
+  };
+  // the long segments' kernels last, but forked before the first group runs on `s`
+  if (L.nlong_max && fork(aux[kSegGroups]) != hipSuccess) return hip_fail(e, "segmented sort: fork");
+  for (int pass = 0; any && pass < 2; ++pass) {  // the side groups fork first, then the group on `s`
+    first = true;
+    for (int g = 0; g < kSegGroups; ++g) {
+      if (grp[g].cls_lo > grp[g].cls_hi || grp[g].cls_hi <= kSegTileClass) continue;
+      const bool side = !first;
       first = false;
-      continue;
+      if (side != (pass == 0)) continue;
+      const dim3 grid(seg_workgroups(grp[g], (uint32_t)nseg));
+      if (!side) {
+        launch_seg_group(grp[g], grid, s, order, 0u, ~0u, g, ctl);
+        continue;
+      }
+      if (fork(aux[g]) != hipSuccess) return hip_fail(e, "segmented sort: fork");
+      launch_seg_group(grp[g], grid, aux[g], order, 0u, ~0u, g, ctl);
+      e = hipEventRecord(ev_join[g], aux[g]);
+      if (e != hipSuccess) return hip_fail(e, "segmented sort: join");
     }
-    e = hipStreamWaitEvent(aux[g], ev_fork, 0);
-    if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent(fork)");
-    launch_seg_group(grp[g], grid, aux[g], order, 0u, ~0u, g, ctl);
-    e = hipEventRecord(ev_join[g], aux[g]);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s, ev_join[g], 0);
-    if (e != hipSuccess) return hip_fail(e, "segmented sort: join");
   }
-  // Long segments: bucket counts, plans, four device-wide passes and the copy back, on a stream of
-  // their own beside the group kernels.
+  // Long segments: bucket counts, plans, four device-wide passes, on a stream of their
+  // own beside the group kernels.
   if (L.nlong_max) {
     hipStream_t ls = aux[kSegGroups];
-    e = hipStreamWaitEvent(ls, ev_fork, 0);
-    if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent(fork)");
     const uint32_t gp = std::min<uint32_t>(L.nlong_max, (uint32_t)(4 * cus));
-    const uint32_t gc = std::min<uint32_t>(L.tiles_max, (uint32_t)(4 * cus));
     if (atomic_rank) {
       hipLaunchKernelGGL((k_seg_long_hist<32768>), dim3(cus), dim3(1024), 0, ls, ctl, longs, lhist, lstatus,
                          L.status_pass_words);
@@ -394,7 +411,6 @@ ap_status enqueue_segmented(uint32_t* d_keys, size_t n_total, const uint32_t* d_
                            lbase, lstatus + (size_t)d * L.status_pass_words, d);
       hipLaunchKernelGGL((k_seg_long_pass<16, 32, RANK_ATOMIC, true>), dim3(cus), dim3(1024), 0, ls, ctl, longs,
                          lbase, lstatus + (size_t)3 * L.status_pass_words, 3);
-      hipLaunchKernelGGL((k_seg_long_copy<32768>), dim3(gc), dim3(256), 0, ls, ctl, longs);
     } else {
       hipLaunchKernelGGL((k_seg_long_hist<16384>), dim3(cus), dim3(1024), 0, ls, ctl, longs, lhist, lstatus,
                          L.status_pass_words);
@@ -404,13 +420,21 @@ ap_status enqueue_segmented(uint32_t* d_keys, size_t n_total, const uint32_t* d_
                            lbase, lstatus + (size_t)d * L.status_pass_words, d);
       hipLaunchKernelGGL((k_seg_long_pass<8, 32, RANK_MATCH, true>), dim3(cus), dim3(512), 0, ls, ctl, longs, lbase,
                          lstatus + (size_t)3 * L.status_pass_words, 3);
-      hipLaunchKernelGGL((k_seg_long_copy<16384>), dim3(gc), dim3(256), 0, ls, ctl, longs);
     }
     e = hipEventRecord(ev_join[kSegGroups], ls);
     if (e == hipSuccess) e = hipStreamWaitEvent(s, ev_join[kSegGroups], 0);
     if (e != hipSuccess) return hip_fail(e, "segmented sort: join");
   }
-  seg_reset(s, ctl);
+  first = true;
+  for (int g = 0; any && g < kSegGroups; ++g) {
+    if (grp[g].cls_lo > grp[g].cls_hi || grp[g].cls_hi <= kSegTileClass) continue;
+    if (!first) e = hipStreamWaitEvent(s, ev_join[g], 0);
+    if (e != hipSuccess) return hip_fail(e, "segmented sort: join");
+    first = false;
+  }
+  const dim3 gf(std::max(1u, std::min<uint32_t>(L.tiles_max, (uint32_t)cus)));
+  if (atomic_rank) hipLaunchKernelGGL((k_seg_finish<32768>), gf, dim3(256), 0, s, ctl, longs);
+  else hipLaunchKernelGGL((k_seg_finish<16384>), gf, dim3(256), 0, s, ctl, longs);
   prof_end(s);
   (void)cfg;
   return check_launch(s, "k_seg_sort");

@@ -25,10 +25,18 @@ namespace aps {
 // power-of-two lengths fill their tile exactly.
 __device__ __forceinline__ int seg_class(uint32_t len) { return 32 - __clz(len - 1u); }
 
+// Segments of at most kSegWaveMax keys are sorted by one wave each, of at most kSegTileMax by one
+// small workgroup each (k_seg_tiles), in the order of the offsets; longer ones are put into length
+// classes and sorted by the groups' workgroups.
+constexpr uint32_t kSegWaveMax = 1024;
+constexpr int kSegTileClass = 12;  // longest length class that k_seg_tiles sorts
+constexpr uint32_t kSegTileMax = 1u << kSegTileClass;
+
 // Pass 1: validate offsets (off[s] <= off[s+1] <= n_total for every s), count segments per length
 // class; the last workgroup turns the counts into a longest-first order of classes, or into an
 // empty order when any offset was invalid, and reports the outcome through d_status.  Segments of
-// long_min keys or more are not counted: they are sorted by the device-wide passes.
+// long_min keys or more are not counted: they are sorted by the device-wide passes.  Nor are the
+// short ones of k_seg_tiles.
 __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t* __restrict__ off, uint32_t nseg,
                                                      uint32_t n_total, uint32_t long_min, SegCtl* __restrict__ ctl,
                                                      uint32_t* __restrict__ d_status) {
@@ -46,100 +54,134 @@ __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t* __restrict
       continue;
     }
     const uint32_t len = b - a;
-    if (len >= 2 && len < long_min) atomicAdd(&s_cnt[seg_class(len)], 1u);
+    if (len > kSegTileMax && len < long_min) atomicAdd(&s_cnt[seg_class(len)], 1u);
   }
   __syncthreads();
   if (tid < kSegBuckets && s_cnt[tid]) add_agent(&ctl->count[tid], s_cnt[tid]);
   if (tid == 0 && s_bad) atomicOr(&ctl->bad, 1u);
+  wait_vmem();  // the counts are complete before this workgroup counts itself done
   __syncthreads();
-  if (tid == 0) {
-    __threadfence();
-    s_last = (add_agent(&ctl->done, 1u) == gridDim.x - 1);
-    if (s_last) __threadfence();
-  }
+  if (tid == 0) s_last = (add_agent(&ctl->done, 1u) == gridDim.x - 1);
   __syncthreads();
   if (!s_last) return;
-  if (tid == 0) {
+  if (tid < (uint32_t)kSegBuckets) {
     // Any invalid offset makes segments overlap or leave the buffer: then nothing is sorted.
     const uint32_t bad = ld_agent(&ctl->bad);
-    uint32_t run = 0;
-    for (int c = kSegBuckets - 1; c >= 0; --c) {  // longest class first
-      const uint32_t k = bad ? 0u : ld_agent(&ctl->count[c]);
-      ctl->count[c] = k;
-      ctl->start[c] = run;
-      run += k;
+    const uint32_t c = kSegBuckets - 1 - tid;  // longest class first
+    const uint32_t k = bad ? 0u : ld_agent(&ctl->count[c]);
+    uint32_t run = k;  // every class at once: an inclusive scan over the lanes
+#pragma unroll
+    for (int o = 1; o < kSegBuckets; o <<= 1) {
+      const uint32_t y = __shfl_up(run, o, kSegBuckets);
+      if (tid >= (uint32_t)o) run += y;
     }
-    ctl->nwork = run;
-    ctl->done = 0u;
-    if (d_status) d_status[0] = bad ? (uint32_t)AP_ERR_INVALID : 0u;
+    ctl->count[c] = k;
+    ctl->start[c] = run - k;
+    if (tid == kSegBuckets - 1) ctl->nwork = run;
+    if (tid == 0) {
+      ctl->done = 0u;
+      if (d_status) d_status[0] = bad ? (uint32_t)AP_ERR_INVALID : 0u;
+    }
   }
 }
 
-// Pass 2: write a descriptor for each valid segment into its class's slots of the work order
-// (in place: src == dst == keys + offset, scratch at the same offset of tmp).  A segment of
-// long_min keys or more gets a LongSeg slot and a range of flat tiles of long_tile keys instead;
-// both come from one 64-bit counter, so flat tile ranges increase with the slot.
-// Slots of the work order are claimed once per wave and class: the lanes of a wave whose
-// segments share a class take consecutive slots from one atomic add of their count.  (With one
-// add per segment, tens of thousands of segments of one class, as the buckets of the bucketing
-// sort are, serialize on that class's counter: ~250 us for 32K segments.)
-__global__ __launch_bounds__(256) void k_seg_fill(const uint32_t* __restrict__ off, uint32_t nseg, uint32_t n_total,
-                                                 uint32_t long_min, uint32_t long_tile, SegCtl* __restrict__ ctl,
-                                                 uint32_t* keys, uint32_t* tmp, SegDesc* __restrict__ order,
-                                                 LongSeg* __restrict__ longs, uint32_t* __restrict__ long_hist) {
+// Sorts keys[0..len) in place with WAVES waves, len <= WAVES * 64 * I.
+template <int WAVES, int RANK, int I = 16>
+__device__ __forceinline__ void seg_tile_sort(const BlockSortLds& lds, gptr<uint32_t> keys, uint32_t len) {
+  if constexpr (I > (WAVES == 1 ? 1 : 4)) {  // the workgroup's shortest tile has more than a wave's 1024 keys
+    constexpr int S = I == 16 ? 12 : I == 12 ? 8 : I == 8 ? 6 : I == 6 ? 4 : I / 2;
+    if (len <= (uint32_t)(WAVES * 64 * S)) {
+      seg_tile_sort<WAVES, RANK, S>(lds, keys, len);
+      return;
+    }
+  }
+  const uint32_t tid = fresh_tid();
+  uint32_t k[I];
+  block_load<WAVES, I>(keys, len, k, tid);
+  const uint32_t first = WAVES == 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)k[0]) : (uint32_t)keys[0];
+  const uint32_t diff = varying_bits<WAVES, I>(k, first, len, lds.scan, tid);
+  if (!diff) return;
+  block_sort<WAVES, I, RANK>(lds, k, diff, tid);
+  block_store<WAVES, I>(keys, len, k, tid);
+}
+
+// Pass 2, a workgroup per `chunk` consecutive segments (chunk <= 64):
+// - segments too long for it get a descriptor in their class's slots of the work order (in place:
+//   src == dst == keys + offset, scratch at the same offset of tmp); a segment of long_min keys or
+//   more gets a LongSeg slot and a range of flat tiles of long_tile keys instead, both from one
+//   64-bit counter, so flat tile ranges increase with the slot;
+// - segments of up to 1024 keys are sorted by one wave each: the tile sort of one wave needs no
+//   barrier, so a wave never waits for its neighbours' longer segments, and the waves of a CU hide
+//   each other's LDS round trips;
+// - then the ones of up to 4096 keys, one after another, by the workgroup.
+// Both sorts use the same 24 KiB of LDS.  16384 segments of 16 to 4096 keys: workgroups with 2048- and
+// 4096-key tiles in two kernels, taking segments one by one from a counter, took 320 us, this kernel
+// takes 80.  What bounds it is the LDS work of the four digit passes (about 45 us of a CU's LDS at
+// these sizes) and its round trips, with 16 waves per CU to hide them: the 16-key tiles take 81 to 99
+// registers, and bounded to 96 or 80 for 20 or 24 waves they spill (2% and 6% slower).
+template <int RANK>
+__global__ __launch_bounds__(256, 4) void k_seg_tiles(const uint32_t* __restrict__ off, uint32_t nseg, uint32_t chunk,
+                                                  uint32_t long_min, uint32_t long_tile, SegCtl* __restrict__ ctl,
+                                                  uint32_t* keys, uint32_t* tmp, SegDesc* __restrict__ order,
+                                                  LongSeg* __restrict__ longs, uint32_t* __restrict__ long_hist) {
+  __shared__ __align__(16) uint32_t s_stage[kSegTileMax];
+  __shared__ __align__(16) uint32_t s_cnt[4 * kBlockRadix], s_off[4 * kBlockRadix];
+  __shared__ uint32_t s_scan[4];
   if (ctl->bad) return;  // invalid offsets: no work
-  const int lane = threadIdx.x & 63;
-  // the loop bound is uniform over the workgroup, so every lane of a wave takes part in the ballots
-  for (uint32_t s0 = blockIdx.x * 256; s0 < nseg; s0 += gridDim.x * 256) {
-    const uint32_t s = s0 + threadIdx.x;
-    int c = -1;  // class of this lane's short segment, -1 if none
-    uint32_t a = 0u, len = 0u;
-    if (s < nseg) {
-      a = off[s];
-      const uint32_t b = off[s + 1];
-      if (b >= a && b <= n_total && b - a >= 2u) {
-        len = b - a;
-        if (len >= long_min) {
-          const uint32_t nt = (len + long_tile - 1) / long_tile;
-          const unsigned long long got = __hip_atomic_fetch_add(&ctl->long_cursor, (1ull << 32) | nt,
-                                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          const uint32_t slot = (uint32_t)(got >> 32);
-          LongSeg& ls = longs[slot];
-          ls.keys = keys + a;
-          ls.tmp = tmp + a;
-          ls.n = len;
-          ls.first_tile = (uint32_t)got;
-          ls.ntiles = nt;
-          // The slot's bucket counts start at zero: where they sit in the workspace depends on
-          // the call's sizes, so nothing a previous call left there can be trusted.
-          uint4* h = reinterpret_cast<uint4*>(long_hist + (size_t)slot * 1024);
-          for (int i = 0; i < 256; ++i) h[i] = make_uint4(0u, 0u, 0u, 0u);
-        } else {
-          c = seg_class(len);
-        }
-      }
+  const uint32_t lane = threadIdx.x & 63u, wid = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t s0 = blockIdx.x * chunk, ns = min(chunk, nseg - s0);
+  // every wave holds the chunk's segments, one per lane
+  uint32_t at = 0u, len = 0u;
+  if (lane < ns) {
+    at = off[s0 + lane];
+    len = off[s0 + lane + 1u] - at;
+  }
+  if (wid == 0u && len > kSegTileMax) {
+    if (len < long_min) {
+      const int c = seg_class(len);
+      SegDesc dsc;
+      dsc.src = keys + at;
+      dsc.dst = keys + at;
+      dsc.tmp = tmp + at;
+      dsc.spl = nullptr;
+      dsc.n = len;
+      dsc.P = 1u;
+      dsc.pad[0] = dsc.pad[1] = 0u;
+      order[ctl->start[c] + add_agent(&ctl->cursor[c], 1u)] = dsc;
+    } else {
+      const uint32_t nt = (len + long_tile - 1) / long_tile;
+      const unsigned long long got = __hip_atomic_fetch_add(&ctl->long_cursor, (1ull << 32) | nt, __ATOMIC_RELAXED,
+                                                            __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t slot = (uint32_t)(got >> 32);
+      LongSeg& ls = longs[slot];
+      ls.keys = keys + at;
+      ls.tmp = tmp + at;
+      ls.n = len;
+      ls.first_tile = (uint32_t)got;
+      ls.ntiles = nt;
+      // The slot's bucket counts start at zero: where they sit in the workspace depends on the
+      // call's sizes, so nothing a previous call left there can be trusted.
+      uint4* h = reinterpret_cast<uint4*>(long_hist + (size_t)slot * 1024);
+      for (int i = 0; i < 256; ++i) h[i] = make_uint4(0u, 0u, 0u, 0u);
     }
-    uint64_t todo = __builtin_amdgcn_ballot_w64(c >= 0);
-    while (todo) {
-      const int leader = __builtin_ctzll(todo);  // wave-uniform
-      const int cl = __builtin_amdgcn_readlane(c, leader);
-      const uint64_t same = __builtin_amdgcn_ballot_w64(c == cl);
-      uint32_t first = 0u;
-      if (lane == leader) first = ctl->start[cl] + add_agent(&ctl->cursor[cl], (uint32_t)__popcll(same));
-      first = (uint32_t)__builtin_amdgcn_readlane((int)first, leader);
-      if (c == cl) {
-        SegDesc dsc;
-        dsc.src = keys + a;
-        dsc.dst = keys + a;
-        dsc.tmp = tmp + a;
-        dsc.spl = nullptr;
-        dsc.n = len;
-        dsc.P = 1u;
-        dsc.pad[0] = dsc.pad[1] = 0u;
-        order[first + lanes_below(same)] = dsc;
-      }
-      todo &= ~same;
+  }
+  {
+    const BlockSortLds lds{s_stage + wid * kSegWaveMax, s_cnt + wid * kBlockRadix, nullptr, nullptr, nullptr};
+    for (uint32_t i = wid; i < ns; i += 4u) {
+      const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)at, (int)i);
+      const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)len, (int)i);
+      if (n >= 2u && n <= kSegWaveMax) seg_tile_sort<1, RANK>(lds, gmem(keys) + a, n);
     }
+  }
+  uint64_t todo = __builtin_amdgcn_ballot_w64(len > kSegWaveMax && len <= kSegTileMax);  // the same in every wave
+  const BlockSortLds lds{s_stage, s_cnt, s_off, s_scan, nullptr};
+  while (todo) {
+    const int i = __builtin_ctzll(todo);
+    todo &= todo - 1u;
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)at, i);
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)len, i);
+    __syncthreads();  // the LDS of the waves' own sorts, or of the segment before, is free
+    seg_tile_sort<4, RANK>(lds, gmem(keys) + a, n);
   }
 }
 
@@ -225,12 +267,13 @@ __device__ __forceinline__ void seg_sort_one_tile(SegSmem<BITS, WAVES, IPT, LCOP
   const gptr<const uint32_t> in = gmem(dsc.src);
   const gptr<uint32_t> out = gmem(dsc.dst);
   const BlockSortLds lds{sm.u.p.stage, sm.u.p.cnt, sm.base, sm.scan, nullptr};
+  const uint32_t tid = fresh_tid();
   uint32_t k[I];
-  block_load<WAVES, I>(in, len, k);
+  block_load<WAVES, I>(in, len, k, tid);
   const uint32_t first = len ? in[0] : 0u;
-  const uint32_t diff = varying_bits<WAVES, I>(k, first, len, sm.scan);
-  block_sort<WAVES, I, RANK>(lds, k, diff);
-  block_store<WAVES, I>(out, len, k);
+  const uint32_t diff = varying_bits<WAVES, I>(k, first, len, sm.scan, tid);
+  block_sort<WAVES, I, RANK>(lds, k, diff, tid);
+  block_store<WAVES, I>(out, len, k, tid);
   if (dsc.spl) {
     // From LDS: the last digit pass left the sorted tile in the stage (with no pass every key is
     // the first one).  Reading them back from memory waits for the stores above and then for the
@@ -265,7 +308,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_sort_small(const uint32_t* src, 
 // work order (classes are stored longest first); otherwise it is [item_lo, item_hi).  Work items
 // are taken from ctl->head[grp].
 template <int BITS, int WAVES, int IPT, int LCOPIES, int RANK>
-__global__ __launch_bounds__(WAVES * 64) void k_seg_sort(const SegDesc* __restrict__ order, uint32_t item_lo,
+__global__ __launch_bounds__(WAVES * 64, 4) void k_seg_sort(const SegDesc* __restrict__ order, uint32_t item_lo,
                                                         uint32_t item_hi, int cls_lo, int cls_hi, int grp,
                                                         SegCtl* __restrict__ ctl) {
   using SM = SegSmem<BITS, WAVES, IPT, LCOPIES>;
@@ -278,6 +321,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_seg_sort(const SegDesc* __restri
     lo = ctl->start[cls_hi];
     hi = ctl->start[cls_lo] + ctl->count[cls_lo];
   }
+  // Workgroups beyond the items leave before they claim or count themselves out: several hundred of
+  // them on one counter took 19 us when a group had no segment at all.
+  const uint32_t nwg = min(gridDim.x, hi > lo ? hi - lo : 0u);
+  if (blockIdx.x >= nwg) return;
 
   while (true) {
     __syncthreads();
@@ -408,30 +455,14 @@ __global__ __launch_bounds__(WAVES * 64) void k_seg_sort(const SegDesc* __restri
     seg_splitters<THREADS>(dsc, len);
   }
 
-  // last workgroup out resets this group's counters for the next call
+  // Last workgroup out resets this group's counters for the next call.  Each workgroup's last claim has
+  // returned (it ended the loop) before it counts itself out, so no claim follows the reset.
   if (tid == 0) {
-    __threadfence();
-    if (add_agent(&ctl->done2[grp], 1u) == gridDim.x - 1) {
+    if (add_agent(&ctl->done2[grp], 1u) == nwg - 1u) {
       st_agent(&ctl->head[grp], 0u);
       st_agent(&ctl->done2[grp], 0u);
     }
   }
-}
-
-// Clears the per-call part of the control block after every group kernel has run.
-__global__ void k_seg_reset(SegCtl* __restrict__ ctl) {
-  const int t = threadIdx.x;
-  if (t < kSegBuckets) {
-    ctl->count[t] = 0u;
-    ctl->start[t] = 0u;
-    ctl->cursor[t] = 0u;
-  }
-  if (t == 0) {
-    ctl->nwork = 0u;
-    ctl->bad = 0u;
-    ctl->long_cursor = 0ull;
-  }
-  if (t < 4) ctl->long_ctr[t] = 0u;
 }
 
 }  // namespace aps

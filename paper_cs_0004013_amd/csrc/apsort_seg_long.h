@@ -200,10 +200,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_seg_long_pass(SegCtl* __restrict
   }
 }
 
-// Copy back: the segments whose sorted keys ended in their scratch (an odd number of passes).
+// After every other kernel of the batch: copies back the long segments whose sorted keys ended in
+// their scratch (an odd number of passes), and the last workgroup clears the per-call part of the
+// control block for the next call.
 template <int TILE>
-__global__ __launch_bounds__(256) void k_seg_long_copy(const SegCtl* __restrict__ ctl,
-                                                      const LongSeg* __restrict__ longs) {
+__global__ __launch_bounds__(256) void k_seg_finish(SegCtl* __restrict__ ctl, const LongSeg* __restrict__ longs) {
+  __shared__ int s_last;
   const unsigned long long cur = ld_agent_u64(&ctl->long_cursor);
   const uint32_t nlong = (uint32_t)(cur >> 32), ntiles = (uint32_t)cur;
   for (uint32_t f = blockIdx.x; f < ntiles; f += gridDim.x) {
@@ -214,6 +216,24 @@ __global__ __launch_bounds__(256) void k_seg_long_copy(const SegCtl* __restrict_
     const uint32_t k1 = min(ls.n, k0 + (uint32_t)TILE);
     const gptr<uint32_t> keys = gmem(ls.keys), tmp = gmem(ls.tmp);
     for (uint32_t i = k0 + threadIdx.x; i < k1; i += 256) keys[i] = tmp[i];
+  }
+  // a workgroup counts itself done after its read of the cursor, so the clear below comes after all
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = add_agent(&ctl->done, 1u) == gridDim.x - 1u;
+  __syncthreads();
+  if (!s_last) return;
+  const uint32_t t = threadIdx.x;
+  if (t < (uint32_t)kSegBuckets) {
+    ctl->count[t] = 0u;
+    ctl->start[t] = 0u;
+    ctl->cursor[t] = 0u;
+  }
+  if (t < 4u) ctl->long_ctr[t] = 0u;
+  if (t == 0u) {
+    ctl->nwork = 0u;
+    ctl->bad = 0u;
+    ctl->done = 0u;
+    ctl->long_cursor = 0ull;
   }
 }
 

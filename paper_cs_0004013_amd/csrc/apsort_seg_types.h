@@ -20,7 +20,7 @@ struct SegCtl {
   uint32_t head[kSegGroups];     // next work item of each length group's kernel
   uint32_t done2[kSegGroups];    // exit counters of each group's kernel
   // long segments (sorted by device-wide passes over one flat tile space)
-  unsigned long long long_cursor;  // (long segments << 32) | flat tiles, advanced by k_seg_fill
+  unsigned long long long_cursor;  // (long segments << 32) | flat tiles, advanced by k_seg_tiles
   uint32_t long_ctr[4];            // tile claim counters of the four digit passes
 };
 

@@ -46,3 +46,21 @@ def test_tile_edges(kind, rank_mode):
         assert np.array_equal(to_host(t), oracle.sort_segmented(keys, off.astype(np.uint64)))
     finally:
         binding.ap_set_rank_mode(0)
+
+
+# a workgroup takes nseg / (24 per CU) segments, at most 64: below, between and above those bounds
+@pytest.mark.parametrize("nseg,hi", [(12287, 700), (20000, 4200), (400_003, 40)])
+def test_many_short_segments(nseg, hi):
+    torch = torch_cuda()
+    from paper_cs_0004013_amd import binding
+    rng = np.random.default_rng(nseg)
+    lens = rng.integers(0, hi + 1, size=nseg)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint32)
+    keys = rng.integers(0, 1 << 32, size=int(off[-1]), dtype=np.uint64).astype(np.uint32)
+    announce(f"short segments nseg={nseg} n={keys.size}")
+    t, _ = to_dev(keys, 1)
+    st = torch.full((1,), 99, dtype=torch.int32, device="cuda")
+    binding.ap_sort_u32_segmented(t, torch.from_numpy(off.view(np.int32)).to("cuda"), st)
+    torch.cuda.synchronize()
+    assert int(st[0]) == 0
+    assert np.array_equal(to_host(t), oracle.sort_segmented(keys, off.astype(np.uint64)))
