@@ -127,14 +127,32 @@ def check(status: int, where: str) -> None:
         raise ApError(status, where, last_error())
 
 
-def _torch():
+# What a call needs of torch, looked up once: a short sort takes 4 us of GPU time, and imports and
+# wrapper objects on the way to the library took 4 us more than the call itself.
+_KEY_DTYPES: tuple = ()
+_raw_stream = None
+
+
+def _bind_torch() -> None:
+    global _KEY_DTYPES, _raw_stream
     import torch
-    return torch
+    get_device = getattr(torch._C, "_cuda_getDevice", None)
+    get_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+    def raw_stream() -> int:
+        # an uninitialised torch.cuda (or a torch without these two) takes the public way
+        if get_device is None or get_stream is None or not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return get_stream(get_device())
+
+    _raw_stream = raw_stream
+    _KEY_DTYPES = (torch.int32, torch.uint32)
 
 
 def _keys_ptr(t, name: str) -> int:
-    torch = _torch()
-    if t.dtype not in (torch.int32, torch.uint32):
+    if not _KEY_DTYPES:
+        _bind_torch()
+    if t.dtype not in _KEY_DTYPES:
         raise TypeError(f"{name}: int32/uint32 tensor expected, got {t.dtype}")
     if not t.is_cuda:
         raise TypeError(f"{name}: device tensor expected")
@@ -144,9 +162,10 @@ def _keys_ptr(t, name: str) -> int:
 
 
 def _stream(stream) -> int:
-    torch = _torch()
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is None:
+            _bind_torch()
+        return _raw_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
