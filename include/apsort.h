@@ -71,8 +71,8 @@ typedef enum {
  *
  * Digit columns whose value is the same for every key are not sorted on (the
  * pass is an identity); this is decided on the device, with no host sync.
- * Arrays of at most 16384 keys are sorted in one launch by one workgroup in
- * registers and LDS, with no scratch memory.  Arrays of up to 9 * 2^17 keys
+ * Arrays of at most 16384 keys are sorted in one launch in registers and LDS
+ * (by one workgroup, or several that each sort a share), with no scratch memory.  Arrays of up to 9 * 2^17 keys
  * are split into cells of neighbouring keys (at splitters drawn from a sample)
  * and every cell is sorted by one workgroup, two launches; longer ones take
  * the device-wide digit passes.  Their scratch memory (about 4n bytes plus the scan state)

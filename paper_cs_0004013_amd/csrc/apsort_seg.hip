@@ -11,6 +11,7 @@
 
 #include "apsort.h"
 #include "apsort_internal.h"
+#include "apsort_ranks.h"
 #include "apsort_seg_kernels.h"
 #include "apsort_seg_long.h"
 
@@ -137,8 +138,9 @@ int seg_workgroups(const SegGroup& g, uint32_t nwork) {
 
 int seg_tile_keys(int cfg) { return kSegCfgs[cfg].waves * 64 * kSegCfgs[cfg].ipt; }
 
-// Single-array sort of n <= kSmallSortMax keys in one launch (one workgroup, keys in registers and
-// LDS).  Few waves for few keys: a pass's scan and barriers grow with the waves, its rank and
+// Single-array sort of n <= kSmallSortMax keys in one launch, keys in registers and LDS: one workgroup,
+// or above 4096 keys, out of place, 16 that each sort a share (apsort_ranks.h; with 8 or 24 the
+// 12345-key sort takes 11.8 or 11.1 us, with 16 11.0).  Few waves for few keys: a pass's scan and barriers grow with the waves, its rank and
 // reorder with the keys per lane.  Microseconds per launch, launches back to back (an empty kernel
 // takes 1.55): 1024 keys 3.9 with 4 waves, 5.2 with 8; 4096 keys 6.7 with 8, 7.7 with 4 or 16; 8192
 // keys 10.3 with 8, 11.1 with 16; 16384 keys 17.7 with 16.
@@ -152,6 +154,14 @@ static void launch_small(hipStream_t s, const uint32_t* in, uint32_t* out, uint3
                        spl);
 }
 
+template <int IPT>
+static void launch_ranks(hipStream_t s, const uint32_t* in, uint32_t* out, uint32_t n, uint32_t P, uint32_t* spl) {
+  if (lane_order_ok())
+    hipLaunchKernelGGL((k_sort_ranks<IPT, SEG_RANK_ATOMIC>), dim3(16), dim3(512), 0, s, in, out, n, P, spl);
+  else
+    hipLaunchKernelGGL((k_sort_ranks<IPT, SEG_RANK_BALLOT>), dim3(16), dim3(512), 0, s, in, out, n, P, spl);
+}
+
 ap_status enqueue_small_sort(const uint32_t* d_in, uint32_t* d_out, size_t n, int P, uint32_t* d_spl,
                              hipStream_t s) {
   if (n > kSmallSortMax) return fail(AP_ERR_INVALID, "small sort takes at most %u keys", kSmallSortMax);
@@ -159,8 +169,10 @@ ap_status enqueue_small_sort(const uint32_t* d_in, uint32_t* d_out, size_t n, in
   uint32_t* spl = P > 1 ? d_spl : nullptr;
   prof_begin(AP_KIND_SEG, s);
   if (n <= 2048) launch_small<4, 8>(s, d_in, d_out, nn, PP, spl);
-  else if (n <= 8192) launch_small<8, 16>(s, d_in, d_out, nn, PP, spl);
-  else launch_small<16, 16>(s, d_in, d_out, nn, PP, spl);
+  else if (n <= 4096 || (n <= 8192 && d_in == d_out)) launch_small<8, 16>(s, d_in, d_out, nn, PP, spl);
+  else if (d_in == d_out) launch_small<16, 16>(s, d_in, d_out, nn, PP, spl);
+  else if (n <= 8192) launch_ranks<16>(s, d_in, d_out, nn, PP, spl);
+  else launch_ranks<32>(s, d_in, d_out, nn, PP, spl);
   prof_end(s);
   return check_launch(s, "k_sort_small");
 }

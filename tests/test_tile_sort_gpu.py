@@ -48,6 +48,37 @@ def test_tile_edges(kind, rank_mode):
         binding.ap_set_rank_mode(0)
 
 
+# the sort by shares of the ranks (4097 to 16384 keys, out of place): keys that put its share ends into
+# one step, one value, the largest value, or past the last key
+@pytest.mark.parametrize("rank_mode", [0, 1])
+@pytest.mark.parametrize("kind", ["full", "bands", "long_tail", "few", "one_outlier", "ends", "half_one_value", "sorted"])
+def test_rank_shares(kind, rank_mode):
+    torch_cuda()
+    from paper_cs_0004013_amd import binding
+    binding.ap_set_rank_mode(rank_mode)
+    try:
+        for n in [4097, 8191, 8192, 8193, 12345, 16383, 16384]:
+            rng = np.random.default_rng(n)
+            full = rng.integers(0, 1 << 32, size=n, dtype=np.uint64).astype(np.uint32)
+            keys = {"full": full,
+                    "bands": ((full & np.uint32(0xF0000000)) | (full & np.uint32(0xFF))).astype(np.uint32),
+                    "long_tail": np.exp(rng.normal(8, 4, n)).clip(0, 4e9).astype(np.uint32),
+                    "few": np.array([5, 5, 5, 9, 0xFFFFFFFF], np.uint32)[full % np.uint32(5)],
+                    "one_outlier": np.where(np.arange(n) == 77, np.uint32(0xFFFFFFFF), full & np.uint32(0xFFF)),
+                    "ends": np.where(full & np.uint32(1), np.uint32(0xFFFFFFFF), np.uint32(0)),
+                    "half_one_value": np.where(full & np.uint32(1), np.uint32(0x12345678), full),
+                    "sorted": np.sort(full)}[kind].astype(np.uint32)
+            announce(f"rank shares n={n} {kind} rank {rank_mode}")
+            out, spl = gpu_sort(keys, 64, pad_front=n % 4)
+            want = oracle.sort_u32(keys)
+            assert np.array_equal(out, want), n
+            assert np.array_equal(spl, oracle.splitters(want, 64)), n
+        out, spl = gpu_sort(keys, 20000)                 # more cells than keys
+        assert np.array_equal(out, want) and np.array_equal(spl, oracle.splitters(want, 20000))
+    finally:
+        binding.ap_set_rank_mode(0)
+
+
 # a workgroup takes nseg / (24 per CU) segments, at most 64: below, between and above those bounds
 @pytest.mark.parametrize("nseg,hi", [(12287, 700), (20000, 4200), (400_003, 40)])
 def test_many_short_segments(nseg, hi):
