@@ -126,9 +126,8 @@ ap_status check_lane_order(hipStream_t s) {
 // Every tile is one workgroup of 16 waves; the tile grows with n (4, 8, 16 then 32 keys per
 // lane).  Larger tiles mean fewer tiles, so the look-back chain between tiles is shorter relative
 // to the time between tile starts, and a bucket's run in a tile is longer, so the scatter writes
-// longer contiguous pieces.  The largest tile (32 keys per lane, 148 KiB of LDS, one workgroup per
-// CU) is used from 2^22 keys on, although below 2^23 keys its 128-255 tiles leave CUs idle: a
-// tile's phases are latency-bound, and fewer, larger tiles finish a pass sooner.  Sixteen waves
+// longer contiguous pieces.  The largest tiles (20 to 32 keys per lane, up to 148 KiB of LDS, one
+// workgroup per CU) are used from 2^22 keys on (shape_for_rounds).  Sixteen waves
 // split a tile's serial work (load, rank, reorder, scatter: one step per key of a lane) into
 // fewer steps than 4 or 8 waves holding the same tile.  Shapes and thresholds are the fastest by
 // measured sort time at every power of two and 1.5 times one from 2^15 to 1.5 * 2^25 keys.
@@ -141,18 +140,32 @@ constexpr uint32_t kHistCopies = kHistMaxCopies;  // copies of the global counte
 struct PassShape {
   int waves, ipt;
 };
-static const PassShape kShapes[] = {{16, 4}, {16, 8}, {16, 16}, {16, 32}};  // 4K, 8K, 16K, 32K keys
+static const PassShape kShapes[] = {{16, 4},  {16, 8},  {16, 16}, {16, 32},   // 4K, 8K, 16K, 32K keys
+                                    {16, 20}, {16, 24}, {16, 28}};            // 20K, 24K, 28K
+
+// From 2^22 keys on a CU holds one tile at a time, and a pass takes as many rounds of tiles as 32K-key
+// tiles need; the smallest tile that needs no more rounds shares the last one's work among all CUs
+// instead of a few.  Microseconds per sort of uniform keys, 32K tiles against that: 4.2M 83.6 / 80.9
+// (20K), 6M 94.4 / 91.6 (24K), 7M 102.1 / 99.7 (28K), 9M 141.6 / 135.4 (20K), 11M 151.7 / 147.8 (24K),
+// 20M 223.9 / 219.1 (28K); one more round costs 20-30% (6M with 20K tiles 120.3).
+static int shape_for_rounds(size_t n) {
+  const size_t round = (size_t)device_cus() * 1024;  // keys of one round per key of a lane
+  const size_t rounds = (n + 32 * round - 1) / (32 * round);
+  for (int sh = 4; sh <= 6; ++sh)
+    if (n <= rounds * round * (size_t)kShapes[sh].ipt) return sh;
+  return 3;
+}
 
 static int shape_for(size_t n) {
-  if (n >= ((size_t)1 << 22)) return 3;
+  if (n >= ((size_t)1 << 22)) return shape_for_rounds(n);
   if (n >= ((size_t)1 << 20)) return 2;
   if (n >= ((size_t)1 << 17)) return 1;
   return 0;
 }
-// The mask rank needs extra LDS that the 32K-key tile cannot spare; it uses the 16K-key shape.
+// The mask rank needs extra LDS that the tiles above 16K keys cannot spare; it uses the 16K-key shape.
 static int shape_for_rank(size_t n, bool atomic_rank) {
   const int sh = shape_for(n);
-  return (!atomic_rank && sh == 3) ? 2 : sh;
+  return (!atomic_rank && sh >= 3) ? 2 : sh;
 }
 static int tile_keys(int sh) { return kShapes[sh].waves * 64 * kShapes[sh].ipt; }
 
@@ -359,7 +372,8 @@ ap_status enqueue_sort_parts(const uint32_t* d_in, uint32_t* d_out, size_t n, in
                    : enqueue_small_sort(d_in, d_out, n, P, d_spl, s);
     if (cells_sort_size(n, pairs)) return enqueue_cells(d_in, d_out, d_vin, d_vout, n, P, d_spl, status, tmp, vtmp, s);
   }
-  const int sh = pairs ? std::min(shape_for_pairs(n), shape_used(n, atomic_rank)) : shape_used(n, atomic_rank);
+  int sh = pairs ? std::min(shape_for_pairs(n), shape_used(n, atomic_rank)) : shape_used(n, atomic_rank);
+  if (!pairs && sh > 3 && dbg.mode != PASS_DBG_NONE) sh = 3;  // the debug kernels are built for four shapes
   const int T = tile_keys(sh);
   const uint32_t ntiles = (uint32_t)((n + T - 1) / T);
   if (ntiles > L.ntiles) return fail(AP_ERR_INVALID, "workspace sized for a larger tile (shape changed after sizing)");
@@ -405,6 +419,18 @@ ap_status enqueue_sort_parts(const uint32_t* d_in, uint32_t* d_out, size_t n, in
     } else {
       switch (sh) {
         case 3: APS_PASS(16, 32, false); break;
+        case 4:
+          launch_pass<16, 20, false, false>(true, grid, s, d_in, d_out, tmp, nn, d, plan, base_d, st_d, tctr, d_vin, d_vout,
+                                            vtmp);
+          break;
+        case 5:
+          launch_pass<16, 24, false, false>(true, grid, s, d_in, d_out, tmp, nn, d, plan, base_d, st_d, tctr, d_vin, d_vout,
+                                            vtmp);
+          break;
+        case 6:
+          launch_pass<16, 28, false, false>(true, grid, s, d_in, d_out, tmp, nn, d, plan, base_d, st_d, tctr, d_vin, d_vout,
+                                            vtmp);
+          break;
         case 2: APS_PASS(16, 16, false); break;
         case 1: APS_PASS(16, 8, false); break;
         default: APS_PASS(16, 4, false); break;

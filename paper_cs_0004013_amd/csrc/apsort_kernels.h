@@ -142,16 +142,12 @@ __global__ __launch_bounds__(THREADS) void k_hist_plan(
     }
     if (c) add_agent(&mine[j], c);
   }
-  // Last-workgroup-done: the barrier makes every thread's adds complete before thread 0's
-  // release fence and completion count; the last workgroup's acquire fence pairs with those
-  // fences.  One thread per workgroup fences (a device-scope fence writes back and invalidates
-  // the L2, so it is kept off the other threads).
+  // Last-workgroup-done: every thread waits for its adds to be performed before the barrier, so they
+  // precede thread 0's completion count; the last workgroup reads the counts where they were added
+  // (agent-scope loads).  No fence: a device-scope one writes back the L2.
+  wait_vmem();
   __syncthreads();
-  if (tid == 0) {
-    __threadfence();
-    s_last = (add_agent(done, 1u) == gridDim.x - 1);
-    if (s_last) __threadfence();
-  }
+  if (tid == 0) s_last = (add_agent(done, 1u) == gridDim.x - 1);
   __syncthreads();
   if (!s_last) return;
 
