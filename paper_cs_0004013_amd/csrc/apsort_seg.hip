@@ -140,8 +140,8 @@ int seg_tile_keys(int cfg) { return kSegCfgs[cfg].waves * 64 * kSegCfgs[cfg].ipt
 
 // Single-array sort of n <= kSmallSortMax keys in one launch, keys in registers and LDS: one workgroup,
 // or above 4096 keys, out of place, 16 that each sort a share (apsort_ranks.h; with 8 or 24 the
-// 12345-key sort takes 11.8 or 11.1 us, with 16 11.0).  Few waves for few keys: a pass's scan and barriers grow with the waves, its rank and
-// reorder with the keys per lane.  Microseconds per launch, launches back to back (an empty kernel
+// 12345-key sort takes 11.8 or 11.1 us, with 16 11.0).  Few waves for few keys: a pass's scan and
+// barriers grow with the waves, its rank and reorder with the keys per lane.  Microseconds per launch, launches back to back (an empty kernel
 // takes 1.55): 1024 keys 3.9 with 4 waves, 5.2 with 8; 4096 keys 6.7 with 8, 7.7 with 4 or 16; 8192
 // keys 10.3 with 8, 11.1 with 16; 16384 keys 17.7 with 16.
 template <int WAVES, int IPT>
@@ -167,10 +167,12 @@ ap_status enqueue_small_sort(const uint32_t* d_in, uint32_t* d_out, size_t n, in
   if (n > kSmallSortMax) return fail(AP_ERR_INVALID, "small sort takes at most %u keys", kSmallSortMax);
   const uint32_t nn = (uint32_t)n, PP = (uint32_t)P;
   uint32_t* spl = P > 1 ? d_spl : nullptr;
+  // one workgroup if anything is written where the keys are read: in place, or splitters into the input
+  const bool one = d_in == d_out || (spl && spl < d_in + n && d_in < spl + (P - 1));
   prof_begin(AP_KIND_SEG, s);
   if (n <= 2048) launch_small<4, 8>(s, d_in, d_out, nn, PP, spl);
-  else if (n <= 4096 || (n <= 8192 && d_in == d_out)) launch_small<8, 16>(s, d_in, d_out, nn, PP, spl);
-  else if (d_in == d_out) launch_small<16, 16>(s, d_in, d_out, nn, PP, spl);
+  else if (n <= 4096 || (n <= 8192 && one)) launch_small<8, 16>(s, d_in, d_out, nn, PP, spl);
+  else if (one) launch_small<16, 16>(s, d_in, d_out, nn, PP, spl);
   else if (n <= 8192) launch_ranks<16>(s, d_in, d_out, nn, PP, spl);
   else launch_ranks<32>(s, d_in, d_out, nn, PP, spl);
   prof_end(s);

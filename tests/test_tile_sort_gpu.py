@@ -79,6 +79,23 @@ def test_rank_shares(kind, rank_mode):
         binding.ap_set_rank_mode(0)
 
 
+def test_rank_shares_splitters_into_the_input():
+    torch = torch_cuda()
+    from paper_cs_0004013_amd import binding
+    for n in [5000, 8192, 12345]:
+        keys = _keys(n, "full")
+        announce(f"splitters into the input, n={n}")
+        for at in (0, n // 2, n - 63):
+            t_in, _ = to_dev(keys)
+            t_out = torch.empty(n, dtype=torch.int32, device="cuda")
+            binding.ap_sort_u32(t_in, t_out, 64, t_in[at:at + 63])
+            torch.cuda.synchronize()
+            want = oracle.sort_u32(keys)
+            assert np.array_equal(to_host(t_out), want), (n, at)
+            assert np.array_equal(to_host(t_in[at:at + 63]), oracle.splitters(want, 64)), (n, at)
+
+
+
 # a workgroup takes nseg / (24 per CU) segments, at most 64: below, between and above those bounds
 @pytest.mark.parametrize("nseg,hi", [(12287, 700), (20000, 4200), (400_003, 40)])
 def test_many_short_segments(nseg, hi):
