@@ -5,11 +5,10 @@
 //
 // Merge path: output position d of the merge of a (na keys) and b (nb keys), ties taking a first,
 // is preceded by exactly split(d) keys of a, the smallest i in [max(0, d - nb), min(d, na)] with
-// NOT (a[i] <= b[d - 1 - i]).  k_merge_partition finds split() at every 64th tile boundary, then
-// at every tile boundary inside those windows (a group of 64, then of 8, lanes per boundary,
-// one candidate per lane and round trip; split() is monotone in d); k_merge_tile then merges one tile of T outputs from the
-// two sub-runs it owns, staged in LDS, each thread merging IPT consecutive outputs after its own
-// search, and writes the tile out coalesced.  Algorithmic bytes: 8 per output key.
+// NOT (a[i] <= b[d - 1 - i]).  k_merge_partition finds split() at every tile boundary (one candidate
+// per lane and round trip); k_merge_tile then merges one tile of T outputs from the two sub-runs it
+// owns, staged in LDS, each thread merging IPT consecutive outputs after its own search, and writes
+// the tile out coalesced.  Algorithmic bytes: 8 per output key.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -58,29 +57,31 @@ __device__ uint32_t merge_split_group(const uint32_t* __restrict__ a, const uint
   return lo + (uint32_t)__popcll(__ballot(p) & gmask);
 }
 
-// splits[t] = split(min(t * step, n)) for t < nsplits, one group of G lanes per entry.  With
-// `coarse` (splits of every ratio-th entry's diagonal, ncoarse of them) each search starts inside
-// its coarse window: the split is monotone in the diagonal.
-template <int G>
-__global__ __launch_bounds__(256) void k_merge_partition(const uint32_t* __restrict__ a, uint32_t na,
-                                                         const uint32_t* __restrict__ b, uint32_t nb,
-                                                         uint32_t* __restrict__ splits, uint32_t nsplits,
-                                                         uint32_t step, const uint32_t* __restrict__ coarse,
-                                                         uint32_t ratio, uint32_t ncoarse) {
-  const uint32_t t = (blockIdx.x * 256u + threadIdx.x) / (uint32_t)G;
-  if (blockIdx.x * 256u + (threadIdx.x & ~63u) >= nsplits * (uint32_t)G) return;  // whole wave past the end
+// splits[t] = split(min(t * T, n)) for t < nsplits; a workgroup finds TILES of them.  First its two waves
+// find the ends of its window, the splits of its first boundary and of the next workgroup's; split() is
+// monotone in the diagonal, so a group of lanes then finds each boundary inside the window.  One launch:
+// windows found by a launch of their own cost 6.8 of 96 us for 2 x 30M keys (now 94), and the launches
+// are most of a short merge (2 x 64K keys 11.1 -> 9.3 us).  Bound by the round trips
+// to memory and by the lines the candidates pull in: 16 waves, fewer round trips, take 109 us.
+constexpr uint32_t kPartThreads = 128;
+
+template <uint32_t TILES>
+__global__ __launch_bounds__(kPartThreads) void k_merge_partition(const uint32_t* __restrict__ a, uint32_t na,
+                                                                  const uint32_t* __restrict__ b, uint32_t nb,
+                                                                  uint32_t* __restrict__ splits, uint32_t nsplits) {
+  constexpr uint32_t G = kPartThreads / TILES;  // lanes per boundary
+  __shared__ uint32_t s_end[2];
+  const uint32_t tid = threadIdx.x, t0 = blockIdx.x * TILES, n = na + nb;
+  const uint32_t de = std::min((t0 + (tid >> 6) * TILES) * kMergeTile, n);
+  const uint32_t end = merge_split_group<64>(a, b, de, de > nb ? de - nb : 0u, std::min(de, na), true);
+  if ((tid & 63u) == 0u) s_end[tid >> 6] = end;
+  __syncthreads();
+  const uint32_t t = t0 + tid / G;
   const bool active = t < nsplits;
-  const uint64_t n = (uint64_t)na + nb;
-  const uint32_t d = active ? (uint32_t)std::min<uint64_t>((uint64_t)t * step, n) : 0u;
-  uint32_t lo = d > nb ? d - nb : 0u;
-  uint32_t hi = d < na ? d : na;
-  if (coarse && active) {
-    const uint32_t c = t / ratio;
-    lo = std::max(lo, coarse[c]);
-    hi = std::min(hi, coarse[std::min(c + 1u, ncoarse - 1u)]);
-  }
-  const uint32_t s = merge_split_group<G>(a, b, d, lo, hi, active);
-  if (active && (threadIdx.x & (uint32_t)(G - 1)) == 0u) splits[t] = s;
+  const uint32_t d = active ? std::min(t * kMergeTile, n) : 0u;
+  const uint32_t lo = std::max(s_end[0], d > nb ? d - nb : 0u), hi = std::min(s_end[1], std::min(d, na));
+  const uint32_t s = merge_split_group<(int)G>(a, b, d, lo, hi, active);
+  if (active && (tid & (G - 1u)) == 0u) splits[t] = s;
 }
 
 // Same search on LDS runs, by one thread (ties: a first).
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_tile(const uint32_t* __
   const uint32_t tid = threadIdx.x, t = blockIdx.x;
   const uint32_t n = na + nb;
   const uint32_t d0 = t * T, d1 = std::min(d0 + T, n);
-  const uint32_t i0 = splits[t], i1 = splits[t + 1];
+  const uint32_t i0 = d0 == 0u ? 0u : splits[t], i1 = d1 == n ? na : splits[t + 1];
   const uint32_t j0 = d0 - i0, j1 = d1 - i1;
   const uint32_t la = i1 - i0, lb = j1 - j0, len = d1 - d0;
   // fixed trip count, loads first: all of a thread's loads are in flight together.  Runs and
@@ -213,26 +214,30 @@ void release_merge_scratch(int dev) {
   g_merge.swap(keep);
 }
 
-constexpr uint32_t kMergeRatio = 64;  // tiles per coarse partition window
+// scratch words: the tile splits
+size_t merge_split_words(size_t n) { return (n + kMergeTile - 1) / kMergeTile + 1; }
 
-// scratch words: the tile splits, then the coarse splits
-size_t merge_split_words(size_t n) {
-  const size_t ntiles = (n + kMergeTile - 1) / kMergeTile;
-  return (ntiles + 1) + (ntiles + kMergeRatio - 1) / kMergeRatio + 1;
+// Boundaries per workgroup by the outputs: the fewer, the more lanes a boundary has (fewer round trips)
+// and the more lines its candidates pull in, which counts once there are many boundaries.  16, 32 and
+// 64 of them, microseconds per merge of two equal runs: 2^23 outputs 17.8 / 18.6 / 20.9, 2^24 34.3 / 34.2
+// / 35.5, 2^27 194 / 189 / 192, 2^29 804 / 770 / 759 (with the windows' own launch 19.1, 35, 192, 762).
+template <uint32_t TILES>
+static void launch_partition(hipStream_t s, const uint32_t* a, uint32_t na, const uint32_t* b, uint32_t nb,
+                             uint32_t* splits, uint32_t nsplits) {
+  hipLaunchKernelGGL(k_merge_partition<TILES>, dim3((nsplits + TILES - 1) / TILES), dim3(kPartThreads), 0, s, a, na, b,
+                     nb, splits, nsplits);
 }
 
 ap_status enqueue_merge(const uint32_t* a, uint32_t na, const uint32_t* b, uint32_t nb, uint32_t* out,
                         uint32_t* splits, hipStream_t s) {
   const uint32_t n = na + nb;
   const uint32_t ntiles = (n + kMergeTile - 1) / kMergeTile;
-  const uint32_t ncoarse = (ntiles + kMergeRatio - 1) / kMergeRatio + 1;
-  uint32_t* coarse = splits + ntiles + 1;
   prof_begin(AP_KIND_MERGE, s);
-  constexpr int kGc = 64, kGf = 8;  // lanes per search: coarse (few, long searches), fine (many, short)
-  hipLaunchKernelGGL(k_merge_partition<kGc>, dim3((ncoarse + 256 / kGc - 1) / (256 / kGc)), dim3(256), 0, s, a, na,
-                     b, nb, coarse, ncoarse, kMergeTile * kMergeRatio, (const uint32_t*)nullptr, 1u, 0u);
-  hipLaunchKernelGGL(k_merge_partition<kGf>, dim3((ntiles + 1 + 256 / kGf - 1) / (256 / kGf)), dim3(256), 0, s, a,
-                     na, b, nb, splits, ntiles + 1, kMergeTile, (const uint32_t*)coarse, kMergeRatio, ncoarse);
+  if (ntiles > 1) {  // one tile has no boundary to find: 2 x 2048 keys in 5.2 us, 6.8 with this launch
+    if (n < (1u << 26)) launch_partition<16>(s, a, na, b, nb, splits, ntiles + 1);
+    else if (n < (1u << 28)) launch_partition<32>(s, a, na, b, nb, splits, ntiles + 1);
+    else launch_partition<64>(s, a, na, b, nb, splits, ntiles + 1);
+  }
   hipLaunchKernelGGL(k_merge_tile, dim3(ntiles), dim3(kMergeThreads), 0, s, a, na, b, nb, splits, out);
   prof_end(s);
   return check_launch(s, "k_merge_tile");
