@@ -332,15 +332,26 @@ static ap_status seg_entry(hipStream_t s, size_t need, SegEntry** out, bool* fre
   return seg_fork_objects(g_seg.back());
 }
 
-// A fresh workspace: zero the control block (offset 0 whatever the sizes; every call leaves it
-// zero again).  Everything else is written by each call before it is read: the long segments'
+// A fresh workspace: zero the control block (offset 0 whatever the sizes; every call leaves what it
+// counts in zero again).  Everything else is written by each call before it is read: the long segments'
 // bucket counts, whose place depends on the call's sizes, are zeroed by k_seg_tiles.
 static ap_status seg_zero_fresh(void* ws, const SegLayout& L, hipStream_t s) {
   char* w = static_cast<char*>(ws);
   return fill_u32(reinterpret_cast<uint32_t*>(w + L.ctl), 0u, up256(sizeof(SegCtl)) / 4, s);
 }
 
-// The launch sequence: classify -> tiles -> groups and long segments side by side -> finish.  No host
+// From this many keys on (or with long segments) the groups run side by side, below it one after
+// another on the caller's stream: an event between streams costs some 10 us, which little work repays.
+// Microseconds per batch, side by side / in sequence: 64 segments of 64 to 512 keys 53 / 17, 100 of 3000
+// 53 / 18, 16 of 5000 53 / 25, 64 of 64 to 64K (650K keys in all) 139 / 142, 256 of those 160 / 163.
+constexpr size_t kSegForkMin = (size_t)1 << 20;
+
+// Where the streams of a batch meet again.  A replayed graph that ends in several kernels costs more
+// than this one at its end (12K keys 49 us, with it 39); on the default stream, never captured, the
+// events are enough.
+__global__ void k_seg_join() {}
+
+// The launch sequence: classify -> tiles -> groups and long segments side by side.  No host
 // synchronisation; every grid size is fixed by (nseg, device), so the sequence can be captured once
 // and replayed.  Launches and the events between streams are what a batch of short segments spends
 // its time on, so nothing is launched that cannot have work: the groups of lengths that k_seg_tiles
@@ -374,14 +385,15 @@ ap_status enqueue_segmented(uint32_t* d_keys, size_t n_total, const uint32_t* d_
     hipLaunchKernelGGL((k_seg_tiles<SEG_RANK_BALLOT>), gt, dim3(256), 0, s, d_off, (uint32_t)nseg, chunk, L.long_min,
                        long_tile, ctl, d_keys, tmp, order, longs, lhist);
   // One persistent kernel per length group.  The groups sort disjoint segments and take work from
-  // counters of their own, so they run concurrently: the first group (longest segments) on `s`,
-  // the others on auxiliary streams forked after k_seg_tiles and joined before the finish.  A
-  // group's workgroups then fill the CUs that another group's tail (its few longest segments)
-  // leaves idle, instead of waiting for that kernel to end.
+  // counters of their own, so in a batch of kSegForkMin keys they run concurrently: the first group
+  // (longest segments) on `s`, the others on auxiliary streams forked after k_seg_tiles and joined at
+  // the end.  A group's workgroups then fill the CUs that another group's tail (its few longest
+  // segments) leaves idle, instead of waiting for that kernel to end.
   SegGroup grp[kSegGroups];
   seg_groups(grp);
   hipError_t e = hipSuccess;
   const bool any = n_total > kSegTileMax;  // some segment may be too long for k_seg_tiles
+  const bool beside = n_total >= kSegForkMin || L.nlong_max;
   bool first = true, forked = false;
   auto fork = [&](hipStream_t side) {
     if (!forked) e = hipEventRecord(ev_fork, s);
@@ -395,7 +407,7 @@ ap_status enqueue_segmented(uint32_t* d_keys, size_t n_total, const uint32_t* d_
     first = true;
     for (int g = 0; g < kSegGroups; ++g) {
       if (grp[g].cls_lo > grp[g].cls_hi || grp[g].cls_hi <= kSegTileClass) continue;
-      const bool side = !first;
+      const bool side = beside && !first;
       first = false;
       if (side != (pass == 0)) continue;
       const dim3 grid(seg_workgroups(grp[g], (uint32_t)nseg));
@@ -409,15 +421,13 @@ ap_status enqueue_segmented(uint32_t* d_keys, size_t n_total, const uint32_t* d_
       if (e != hipSuccess) return hip_fail(e, "segmented sort: join");
     }
   }
-  // Long segments: bucket counts, plans, four device-wide passes, on a stream of their
+  // Long segments: bucket counts and plans, four device-wide passes, on a stream of their
   // own beside the group kernels.
   if (L.nlong_max) {
     hipStream_t ls = aux[kSegGroups];
-    const uint32_t gp = std::min<uint32_t>(L.nlong_max, (uint32_t)(4 * cus));
     if (atomic_rank) {
-      hipLaunchKernelGGL((k_seg_long_hist<32768>), dim3(cus), dim3(1024), 0, ls, ctl, longs, lhist, lstatus,
+      hipLaunchKernelGGL((k_seg_long_hist<32768>), dim3(cus), dim3(1024), 0, ls, ctl, longs, lhist, lbase, lstatus,
                          L.status_pass_words);
-      hipLaunchKernelGGL(k_seg_long_plan, dim3(gp), dim3(256), 0, ls, ctl, longs, lhist, lbase);
       // plain stores before the last pass, the non-temporal hint on it (long segments hold at least
       // 2^20 keys each; the single-array sort does the same from 2^23 keys on)
       for (int d = 0; d < 3; ++d)
@@ -426,9 +436,8 @@ ap_status enqueue_segmented(uint32_t* d_keys, size_t n_total, const uint32_t* d_
       hipLaunchKernelGGL((k_seg_long_pass<16, 32, RANK_ATOMIC, true>), dim3(cus), dim3(1024), 0, ls, ctl, longs,
                          lbase, lstatus + (size_t)3 * L.status_pass_words, 3);
     } else {
-      hipLaunchKernelGGL((k_seg_long_hist<16384>), dim3(cus), dim3(1024), 0, ls, ctl, longs, lhist, lstatus,
+      hipLaunchKernelGGL((k_seg_long_hist<16384>), dim3(cus), dim3(1024), 0, ls, ctl, longs, lhist, lbase, lstatus,
                          L.status_pass_words);
-      hipLaunchKernelGGL(k_seg_long_plan, dim3(gp), dim3(256), 0, ls, ctl, longs, lhist, lbase);
       for (int d = 0; d < 3; ++d)
         hipLaunchKernelGGL((k_seg_long_pass<8, 32, RANK_MATCH, false>), dim3(cus), dim3(512), 0, ls, ctl, longs,
                            lbase, lstatus + (size_t)d * L.status_pass_words, d);
@@ -442,13 +451,11 @@ ap_status enqueue_segmented(uint32_t* d_keys, size_t n_total, const uint32_t* d_
   first = true;
   for (int g = 0; any && g < kSegGroups; ++g) {
     if (grp[g].cls_lo > grp[g].cls_hi || grp[g].cls_hi <= kSegTileClass) continue;
-    if (!first) e = hipStreamWaitEvent(s, ev_join[g], 0);
+    if (beside && !first) e = hipStreamWaitEvent(s, ev_join[g], 0);
     if (e != hipSuccess) return hip_fail(e, "segmented sort: join");
     first = false;
   }
-  const dim3 gf(std::max(1u, std::min<uint32_t>(L.tiles_max, (uint32_t)cus)));
-  if (atomic_rank) hipLaunchKernelGGL((k_seg_finish<32768>), gf, dim3(256), 0, s, ctl, longs);
-  else hipLaunchKernelGGL((k_seg_finish<16384>), gf, dim3(256), 0, s, ctl, longs);
+  if (forked && s) hipLaunchKernelGGL(k_seg_join, dim3(1), dim3(64), 0, s);
   prof_end(s);
   (void)cfg;
   return check_launch(s, "k_seg_sort");

@@ -75,11 +75,15 @@ __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t* __restrict
       const uint32_t y = __shfl_up(run, o, kSegBuckets);
       if (tid >= (uint32_t)o) run += y;
     }
-    ctl->count[c] = k;
     ctl->start[c] = run - k;
-    if (tid == kSegBuckets - 1) ctl->nwork = run;
+    ctl->cursor[c] = 0u;
+    st_agent(&ctl->count[c], 0u);
+    if (tid < 4u) ctl->long_ctr[tid] = 0u;
     if (tid == 0) {
-      ctl->done = 0u;
+      ctl->invalid = bad;
+      ctl->long_cursor = 0ull;
+      st_agent(&ctl->bad, 0u);
+      st_agent(&ctl->done, 0u);
       if (d_status) d_status[0] = bad ? (uint32_t)AP_ERR_INVALID : 0u;
     }
   }
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(256, 4) void k_seg_tiles(const uint32_t* __restrict
   __shared__ __align__(16) uint32_t s_stage[kSegTileMax];
   __shared__ __align__(16) uint32_t s_cnt[4 * kBlockRadix], s_off[4 * kBlockRadix];
   __shared__ uint32_t s_scan[4];
-  if (ctl->bad) return;  // invalid offsets: no work
+  if (ctl->invalid) return;  // invalid offsets: no work
   const uint32_t lane = threadIdx.x & 63u, wid = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t s0 = blockIdx.x * chunk, ns = min(chunk, nseg - s0);
   // every wave holds the chunk's segments, one per lane
@@ -159,6 +163,7 @@ __global__ __launch_bounds__(256, 4) void k_seg_tiles(const uint32_t* __restrict
       ls.n = len;
       ls.first_tile = (uint32_t)got;
       ls.ntiles = nt;
+      ls.counted = 0u;
       // The slot's bucket counts start at zero: where they sit in the workspace depends on the
       // call's sizes, so nothing a previous call left there can be trusted.
       uint4* h = reinterpret_cast<uint4*>(long_hist + (size_t)slot * 1024);
@@ -206,7 +211,7 @@ struct SegSmem {
   alignas(16) uint32_t base[BASE];
   uint32_t running[R];   // next free slot of each bucket in the current digit sweep
   uint32_t lbase[R + 1]; // tile-local bucket starts (+ tile size)
-  uint32_t tot[R];       // tile bucket totals
+  uint32_t shift[R];     // from a bucket's place in the sorted tile to its place in the output (modulo 2^32)
   uint32_t scan[WAVES];
   uint32_t flag[kMaxDigits];
   uint32_t item;
@@ -228,14 +233,17 @@ __device__ __forceinline__ void seg_splitters(const SegDesc& dsc, uint32_t len) 
 }
 
 // Tile rank of the keys k[] (wave-striped order) by the digit at `shift`: per-wave LDS counters,
-// then one scan gives cnt[w][v] = tile-local start of wave w's run of bucket v, lbase (bucket
-// starts) and tot (bucket totals).  RANK: SegRank.
+// then one scan gives cnt[w][v] = tile-local start of wave w's run of bucket v, and each bucket's
+// way from there to the output; running moves on to the next tile's place.  One table for the way: the
+// scatter is bound by the LDS reads that each key costs.  No barrier at the start: the counters were
+// last read before the barrier that the caller's scatter follows.  RANK: SegRank.
 template <int BITS, int WAVES, int IPT, int LCOPIES, int RANK>
 __device__ __forceinline__ void seg_rank_tile(SegSmem<BITS, WAVES, IPT, LCOPIES>& sm, const uint32_t (&k)[IPT],
                                               uint32_t (&r)[IPT], int shift) {
   constexpr int R = 1 << BITS, THREADS = WAVES * 64;
   const int tid = threadIdx.x, wid = tid >> 6;
-  for (int j = tid; j < WAVES * R; j += THREADS) sm.u.p.cnt[j] = 0u;
+  for (int j = tid; j < WAVES * R / 4; j += THREADS)
+    reinterpret_cast<uint4*>(sm.u.p.cnt)[j] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
   uint32_t* cnt = sm.u.p.cnt + wid * R;
   if constexpr (RANK == SEG_RANK_ATOMIC) {
@@ -246,7 +254,11 @@ __device__ __forceinline__ void seg_rank_tile(SegSmem<BITS, WAVES, IPT, LCOPIES>
     for (int j = 0; j < IPT; ++j) r[j] = rank_ballot<BITS>(cnt, (k[j] >> shift) & (R - 1));
   }
   tile_bucket_offsets<R, WAVES>(sm.u.p.cnt, sm.lbase, sm.scan);
-  for (int b = tid; b < R; b += THREADS) sm.tot[b] = sm.lbase[b + 1] - sm.lbase[b];
+  for (int b = tid; b < R; b += THREADS) {
+    const uint32_t at = sm.running[b], start = sm.lbase[b];
+    sm.shift[b] = at - start;
+    sm.running[b] = at + sm.lbase[b + 1] - start;
+  }
   __syncthreads();
 }
 
@@ -304,8 +316,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_sort_small(const uint32_t* src, 
 }
 
 // Persistent segmented sort over the descriptors order[lo..hi), longest first.  With
-// item_hi == ~0u the range is that of the length classes [cls_lo, cls_hi] in the device-built
-// work order (classes are stored longest first); otherwise it is [item_lo, item_hi).  Work items
+// item_hi == ~0u the range is that of the length classes [cls_lo, cls_hi], cls_lo >= 1, in the
+// device-built work order (classes are stored longest first); otherwise it is [item_lo, item_hi).  Work items
 // are taken from ctl->head[grp].
 template <int BITS, int WAVES, int IPT, int LCOPIES, int RANK>
 __global__ __launch_bounds__(WAVES * 64, 4) void k_seg_sort(const SegDesc* __restrict__ order, uint32_t item_lo,
@@ -319,7 +331,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_seg_sort(const SegDesc* __res
   uint32_t lo = item_lo, hi = item_hi;
   if (item_hi == ~0u) {
     lo = ctl->start[cls_hi];
-    hi = ctl->start[cls_lo] + ctl->count[cls_lo];
+    hi = ctl->start[cls_lo - 1];
   }
   // Workgroups beyond the items leave before they claim or count themselves out: several hundred of
   // them on one counter took 19 us when a group had no segment at all.
@@ -436,11 +448,9 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_seg_sort(const SegDesc* __res
           if (i < nvalid) {
             const uint32_t key = sm.u.p.stage[i];
             const uint32_t v = (key >> shift) & (R - 1);
-            dst[sm.running[v] + i - sm.lbase[v]] = key;
+            dst[sm.shift[v] + i] = key;
           }
         }
-        __syncthreads();
-        for (int b = tid; b < R; b += THREADS) sm.running[b] += sm.tot[b];
       }
       src = dst;
       gptr<uint32_t> nxt = other;

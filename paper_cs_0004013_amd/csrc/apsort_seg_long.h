@@ -7,7 +7,8 @@
 // tiles [first_tile, first_tile + ntiles), the look-back of a tile stops at its segment's first
 // tile, and the persistent workgroups of a pass take flat tiles in increasing order from one
 // counter per pass, so tiles of all long segments are in flight together.  Keys are sorted in
-// place through the segment's scratch; an odd number of passes ends with a copy back.
+// place through the segment's scratch; beside an odd number of sorting passes, the pass of a constant
+// digit copies.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,6 +42,37 @@ __device__ __forceinline__ uint32_t long_slot_lds(const uint32_t* first, uint32_
 }
 constexpr uint32_t kLongSlotCache = 512;  // first tiles of up to this many long segments kept in LDS
 
+// Plan of a long segment from its complete bucket counts g, by a workgroup of 1024 threads: the digit
+// passes and their buffers, and the cumulative totals per digit (a digit is 4 waves).  Passes that run
+// read and write the keys and the scratch in turn, from keys to scratch first; if an odd number of digits
+// varies, the pass of the first constant one copies, and the last pass that runs writes the keys.
+__device__ __forceinline__ void long_plan(LongSeg& ls, const uint32_t* g, uint32_t* base, uint32_t n, uint32_t* s_scan,
+                                          uint32_t* s_const) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6;
+  if (tid < 4u) s_const[tid] = 0u;
+  const uint32_t c = ld_agent(&g[tid]);
+  const uint32_t x = wave_incl_scan(c);
+  if (lane == 63u) s_scan[wid] = x;
+  __syncthreads();
+  if (c == n) s_const[wid >> 2] = 1u;  // one bucket holds every key: the digit is constant
+  uint32_t run = x - c;
+#pragma unroll
+  for (uint32_t w = 0; w < 3u; ++w) run += w < (wid & 3u) ? s_scan[(wid & ~3u) + w] : 0u;
+  base[tid] = run;
+  __syncthreads();
+  if (tid == 0u) {
+    bool odd = ((s_const[0] + s_const[1] + s_const[2] + s_const[3]) & 1u) != 0u;
+    uint32_t in_tmp = 0u;
+    for (int d = 0; d < 4; ++d) {
+      const uint32_t todo = !s_const[d] ? LONG_SORT : odd ? LONG_COPY : LONG_SKIP;
+      if (todo == LONG_COPY) odd = false;
+      ls.run[d] = todo;
+      ls.rd_tmp[d] = in_tmp;
+      if (todo != LONG_SKIP) in_tmp ^= 1u;
+    }
+  }
+}
+
 // Bucket counts of every 8-bit digit of every long segment, and zeroed look-back words for every
 // flat tile.  Workgroup w takes a contiguous range of flat tiles (tiles of one segment are mostly
 // counted by few workgroups).  As in k_hist_plan, every lane position l of the wave owns a private
@@ -48,15 +80,18 @@ constexpr uint32_t kLongSlotCache = 512;  // first tiles of up to this many long
 // (B / 2) * 64 + l, so the 64 lanes of one atomic add hit 64 different banks whatever the keys.  A
 // copy counts the keys of 16 threads; the copies are summed into the segment's global counts when
 // the range leaves a segment and after every kLongHistFlush tiles, so that a copy counts at most
-// 16 * kLongHistFlush * TILE / 1024 < 2^16 keys.
+// 16 * kLongHistFlush * TILE / 1024 < 2^16 keys.  The workgroup that completes a segment's counts makes
+// its plan: a launch of its own for that cost every batch without long segments 5 us.
 constexpr uint32_t kLongHistFlush = 32;
 template <int TILE>
 __global__ __launch_bounds__(1024) void k_seg_long_hist(const SegCtl* __restrict__ ctl,
-                                                       const LongSeg* __restrict__ longs,
-                                                       uint32_t* __restrict__ hist, uint32_t* __restrict__ status,
+                                                       LongSeg* __restrict__ longs, uint32_t* __restrict__ hist,
+                                                       uint32_t* __restrict__ base, uint32_t* __restrict__ status,
                                                        size_t status_pass_words) {
   static_assert(16u * kLongHistFlush * (TILE / 1024) < 65536u, "16-bit lane counters would overflow");
   __shared__ uint32_t h[512 * 64];  // 1024 16-bit counters per lane position
+  __shared__ uint32_t s_scan[16], s_const[4];
+  __shared__ int s_all;
   const unsigned long long cur = ld_agent_u64(&ctl->long_cursor);
   const uint32_t nlong = (uint32_t)(cur >> 32), ntiles = (uint32_t)cur;
   if (ntiles == 0u) return;
@@ -105,51 +140,14 @@ __global__ __launch_bounds__(1024) void k_seg_long_hist(const SegCtl* __restrict
       for (uint32_t q = 0; q < 64u; ++q) c += (h[row + ((q + j) & 63u)] >> sh) & 0xFFFFu;
       if (c) add_agent(&g[j], c);
     }
+    wait_vmem();  // the counts are added before their tiles are counted
     __syncthreads();
+    if (tid == 0u) s_all = add_agent(&longs[slot].counted, last - f) + (last - f) == ls.ntiles;
     for (uint32_t x = tid; x < 512u * 64u; x += 1024u) h[x] = 0u;
     __syncthreads();
+    if (s_all) long_plan(longs[slot], g, base + (size_t)slot * 1024, ls.n, s_scan, s_const);
     f = last;
     if (f == seg_end) ++slot;
-  }
-}
-
-// Plan of each long segment from its bucket counts: which digit passes run, their buffers, and the
-// cumulative totals per digit.
-__global__ __launch_bounds__(256) void k_seg_long_plan(const SegCtl* __restrict__ ctl, LongSeg* __restrict__ longs,
-                                                      const uint32_t* __restrict__ hist, uint32_t* __restrict__ base) {
-  __shared__ uint32_t s_h[4 * 256];
-  __shared__ uint32_t s_const[4];
-  __shared__ uint32_t s_scan[4];
-  const uint32_t nlong = (uint32_t)(ld_agent_u64(&ctl->long_cursor) >> 32);
-  const int tid = threadIdx.x;
-  for (uint32_t s = blockIdx.x; s < nlong; s += gridDim.x) {
-    const uint32_t* g = hist + (size_t)s * 1024;
-    const uint32_t n = longs[s].n;
-    if (tid < 4) s_const[tid] = 0u;
-    __syncthreads();
-    for (int j = tid; j < 1024; j += 256) {
-      const uint32_t c = g[j];
-      s_h[j] = c;
-      if (c == n) s_const[j >> 8] = 1u;  // one bucket holds every key: the digit is constant
-    }
-    for (int d = 0; d < 4; ++d) lds_exclusive_scan<256, 256>(s_h + d * 256, s_scan);
-    for (int j = tid; j < 1024; j += 256) base[(size_t)s * 1024 + j] = s_h[j];
-    if (tid == 0) {
-      // in place: the first pass that runs reads the keys and writes the scratch, then they alternate
-      uint32_t npass = 0, in_tmp = 0;
-      for (int d = 0; d < 4; ++d) {
-        const uint32_t run = s_const[d] ? 0u : 1u;
-        longs[s].run[d] = run;
-        longs[s].rd_tmp[d] = in_tmp;
-        if (run) {
-          in_tmp ^= 1u;
-          ++npass;
-        }
-      }
-      longs[s].npass = npass;
-      longs[s].final_tmp = in_tmp;
-    }
-    __syncthreads();
   }
 }
 
@@ -157,8 +155,8 @@ __global__ __launch_bounds__(256) void k_seg_long_plan(const SegCtl* __restrict_
 // that an empty pass costs a few hundred workgroups, not one per possible tile): every workgroup
 // takes the next flat tile from the pass's counter until none is left, so tiles start in
 // increasing order and a look-back only waits on tiles already taken by running workgroups, which
-// each process one tile at a time.  A tile of a segment whose digit is constant is skipped (the
-// whole segment skips the pass, so no tile of it is looked back at).  NT_STORE: the scatter's
+// each process one tile at a time.  A tile of a segment whose digit is constant is skipped or copied (no
+// tile of the segment is looked back at).  NT_STORE: the scatter's
 // store hint (plain for the passes before the last, as in the single-array sort of large arrays).
 template <int WAVES, int IPT, int RANK, bool NT_STORE>
 __global__ __launch_bounds__(WAVES * 64) void k_seg_long_pass(SegCtl* __restrict__ ctl, const LongSeg* __restrict__ longs,
@@ -187,8 +185,13 @@ __global__ __launch_bounds__(WAVES * 64) void k_seg_long_pass(SegCtl* __restrict
     const uint32_t f = s_tile, slot = s_slot;
     if (f >= ntiles) break;
     const LongSeg& ls = longs[slot];
-    if (ls.run[d]) {
-      const uint32_t rd = ls.rd_tmp[d];
+    const uint32_t rd = ls.rd_tmp[d], todo = ls.run[d];
+    if (todo == LONG_COPY) {
+      const uint32_t k0 = (f - ls.first_tile) * (uint32_t)(WAVES * 64 * IPT), k1 = min(ls.n, k0 + WAVES * 64u * IPT);
+      const gptr<const uint32_t> from = gmem(rd ? ls.tmp : ls.keys);
+      const gptr<uint32_t> to = gmem(rd ? ls.keys : ls.tmp);
+      for (uint32_t i = k0 + threadIdx.x; i < k1; i += WAVES * 64u) to[i] = from[i];
+    } else if (todo == LONG_SORT) {
       // an opaque copy of the thread index: see pass_tile
       int tid = (int)threadIdx.x;
       asm volatile("" : "+v"(tid));
@@ -197,43 +200,6 @@ __global__ __launch_bounds__(WAVES * 64) void k_seg_long_pass(SegCtl* __restrict
           base + (size_t)slot * 1024 + d * 256, status + (size_t)ls.first_tile * 256, tid);
     }
     __syncthreads();  // every thread is done with this tile's LDS before the next claim
-  }
-}
-
-// After every other kernel of the batch: copies back the long segments whose sorted keys ended in
-// their scratch (an odd number of passes), and the last workgroup clears the per-call part of the
-// control block for the next call.
-template <int TILE>
-__global__ __launch_bounds__(256) void k_seg_finish(SegCtl* __restrict__ ctl, const LongSeg* __restrict__ longs) {
-  __shared__ int s_last;
-  const unsigned long long cur = ld_agent_u64(&ctl->long_cursor);
-  const uint32_t nlong = (uint32_t)(cur >> 32), ntiles = (uint32_t)cur;
-  for (uint32_t f = blockIdx.x; f < ntiles; f += gridDim.x) {
-    const uint32_t slot = long_slot(longs, nlong, f);
-    const LongSeg& ls = longs[slot];
-    if (!ls.final_tmp) continue;
-    const uint32_t k0 = (f - ls.first_tile) * (uint32_t)TILE;
-    const uint32_t k1 = min(ls.n, k0 + (uint32_t)TILE);
-    const gptr<uint32_t> keys = gmem(ls.keys), tmp = gmem(ls.tmp);
-    for (uint32_t i = k0 + threadIdx.x; i < k1; i += 256) keys[i] = tmp[i];
-  }
-  // a workgroup counts itself done after its read of the cursor, so the clear below comes after all
-  __syncthreads();
-  if (threadIdx.x == 0) s_last = add_agent(&ctl->done, 1u) == gridDim.x - 1u;
-  __syncthreads();
-  if (!s_last) return;
-  const uint32_t t = threadIdx.x;
-  if (t < (uint32_t)kSegBuckets) {
-    ctl->count[t] = 0u;
-    ctl->start[t] = 0u;
-    ctl->cursor[t] = 0u;
-  }
-  if (t < 4u) ctl->long_ctr[t] = 0u;
-  if (t == 0u) {
-    ctl->nwork = 0u;
-    ctl->bad = 0u;
-    ctl->done = 0u;
-    ctl->long_cursor = 0ull;
   }
 }
 

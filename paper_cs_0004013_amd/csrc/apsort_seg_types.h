@@ -8,14 +8,17 @@ namespace aps {
 constexpr int kSegBuckets = 32;  // work-list classes: ceil(log2(length))
 constexpr int kSegGroups = 6;    // length groups, each sorted by its own kernel configuration
 
-// Control block of the segmented sort (device memory, zero between calls).
+// Control block of the segmented sort (device memory, zero at first).  What k_seg_classify adds up
+// (count, done, bad) and what the groups count (head, done2) is zero again when its kernel ends; the rest
+// is set by k_seg_classify's last workgroup, so no kernel at the end of a call has to clear it.
 struct SegCtl {
-  uint32_t count[kSegBuckets];   // segments per length class
-  uint32_t start[kSegBuckets];   // first slot of each class in the work order (longest first)
+  uint32_t count[kSegBuckets];   // segments per length class, while they are counted
+  uint32_t start[kSegBuckets];   // first slot of each class in the work order (longest first); class c ends
+                                 // where class c - 1 starts (class 0 is empty)
   uint32_t cursor[kSegBuckets];  // fill cursors
-  uint32_t nwork;                // segments to sort (length >= 2 and valid)
   uint32_t done;                 // completion counter of k_seg_classify's last-workgroup pattern
-  uint32_t bad;                  // 1 when some offsets were invalid
+  uint32_t bad;                  // some offsets were invalid, while they are checked
+  uint32_t invalid;              // some offsets were invalid: nothing is sorted
   uint32_t pad0;
   uint32_t head[kSegGroups];     // next work item of each length group's kernel
   uint32_t done2[kSegGroups];    // exit counters of each group's kernel
@@ -26,18 +29,18 @@ struct SegCtl {
 
 // A long segment: keys[0..n) sorted in place by device-wide digit passes, through tmp[0..n); its
 // tiles are flat tiles [first_tile, first_tile + ntiles) of the batch.  The plan is written by
-// k_seg_long_plan from the segment's bucket counts.
+// k_seg_long_hist from the segment's bucket counts.
+enum LongRun : uint32_t { LONG_SKIP = 0, LONG_SORT = 1, LONG_COPY = 2 };
 struct LongSeg {
   uint32_t* keys;
   uint32_t* tmp;
   uint32_t n;
   uint32_t first_tile;
   uint32_t ntiles;
-  uint32_t npass;       // digit passes that run
-  uint32_t run[4];      // pass d runs (its digit is not constant over the segment)
+  uint32_t counted;     // tiles whose keys are in the bucket counts
+  uint32_t run[4];      // LongRun of pass d
   uint32_t rd_tmp[4];   // pass d reads tmp and writes keys (else reads keys, writes tmp)
-  uint32_t final_tmp;   // the sorted keys end in tmp and are copied back
-  uint32_t pad[3];
+  uint32_t pad[4];
 };
 
 // One unit of work of the persistent sort: sort src[0..n) into dst[0..n) (src == dst allowed),
