@@ -245,8 +245,8 @@ ap_status ap_digit_plan_u32(const uint32_t *d_in, size_t n, int digit_bits,
  * write of each key); longer ones by the same workgroup with a histogram sweep
  * and one sweep per non-constant digit.  Segments of up to 4096 keys are taken
  * in the order of the offsets, longer ones longest first by persistent
- * kernels, one per length group.  Segments at or above the threshold are sorted like one
- * array, by device-wide digit passes (bucket counts per segment, then one pass
+ * kernels, one per length group.  Segments at or above the threshold are
+ * sorted like one array, by device-wide digit passes (bucket counts per segment, then one pass
  * per non-constant digit with a single-pass scan over the tiles of all long
  * segments), beside the workgroup-per-segment kernels.  No host
  * synchronisation; on a non-default stream the launch sequence is captured
@@ -271,8 +271,8 @@ size_t ap_segmented_get_long_min(void);
 size_t ap_segmented_workspace_bytes(size_t n_total, int nseg);
 
 /*
- * Segmented-sort tuning.  Segments (and batched server requests) fall in
- * length groups: group g covers the lengths whose length class, ceil(log2(length))
+ * Segmented-sort tuning.  Segments of more than 4096 keys (and batched server
+ * requests of any length) fall in length groups: group g covers the lengths whose length class, ceil(log2(length))
  * (lengths 0..2 count as class 1), lies in [cls_lo, cls_hi] and runs kernel
  * configuration cfg (digit width, waves per
  * workgroup, keys per lane; ap_segmented_num_configs() configurations are

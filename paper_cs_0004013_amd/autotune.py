@@ -3,7 +3,8 @@ workgroup, keys per lane) of each length group by measurement.
 
 The length groups are fixed ranges of length classes ceil(log2(segment length)), one per tile
 size: more than 8K keys (16K-key tiles, longer segments by digit sweeps), (4K, 8K], (2K, 4K] and
-up to 2K.  Every group is one more concurrent persistent kernel: classes that run the same
+up to 2K.  A batch's segments of up to 4096 keys have a kernel of their own, so the choice for the last
+two groups matters only to batched server requests and stays within the noise here.  Every group is one more concurrent persistent kernel: classes that run the same
 configuration are better served by one group (a fifth group splitting off the segments above 16K
 measured 1.5-2% slower with the same configurations).  The tuning batch has the workload's shape: 4096 segments with lengths
 log-uniform in [64, 2^18] and distributions (a)-(e) by segment seed; three such batches are
