@@ -1,13 +1,13 @@
 // Device kernels of the batched segmented sort: many independent key arrays (segments) of one
-// buffer, each sorted in place, in one persistent launch.
+// buffer, each sorted in place.
 //
-// Each segment is sorted by one workgroup, the way each AP1000 cell runs its own local radix sort
-// on the keys it holds (Sec. 3.3 / 3.3.1): a segment that fits in one tile is sorted entirely in
+// Each segment is sorted by one wave (up to 1024 keys) or one workgroup, the way each AP1000 cell runs
+// its own local radix sort on the keys it holds (Sec. 3.3 / 3.3.1): a segment that fits in one tile is sorted entirely in
 // registers and LDS (read once, written once); a longer one is sorted by the same workgroup with
 // one LDS histogram sweep over the segment (Sec. 3.2 bucket counts and cumulative totals for all
 // digits) and then, per digit, a sweep over its tiles in order, in which running bucket offsets kept
 // in LDS replace any cross-workgroup scan.  Digits constant over a segment are skipped.  Segments
-// are taken longest first so the longest ones do not finish last.
+// of more than 4096 keys are taken longest first so the longest ones do not finish last.
 #pragma once
 
 #include <hip/hip_runtime.h>
