@@ -32,9 +32,11 @@ constexpr int kLutBits = 11;  // key prefixes of the cell look-up table
 constexpr int kLutSize = 1 << kLutBits;
 
 // Position i (of m) of the sample of n >= m keys: one key out of every n / m, at a scrambled place
-// of its stretch, so that a period in the input does not show in the sample.
-__device__ __forceinline__ uint32_t sample_pos(uint32_t i, uint32_t stride) {
-  uint32_t h = i * 0x9E3779B9u;
+// of its stretch, so that a period in the input does not show in the sample.  The salt, made from the
+// input's address, keeps the places from being the same for every array of a length: keys that differ
+// from all others at known places would put nearly the whole array into one cell.
+__device__ __forceinline__ uint32_t sample_pos(uint32_t i, uint32_t stride, uint32_t salt) {
+  uint32_t h = i * 0x9E3779B9u + salt;
   h ^= h >> 15;
   h *= 0x85EBCA6Bu;
   h ^= h >> 13;
@@ -48,7 +50,8 @@ __device__ __forceinline__ uint32_t sample_pos(uint32_t i, uint32_t stride) {
 // equal; if some are (narrow bands of keys, or a value that fills more than a cell), the whole keys
 // are sorted.
 template <int WAVES, int SI, int B, int RANK>
-__device__ __forceinline__ void split_sample(const BlockSortLds& lds, gptr<const uint32_t> in, uint32_t n, uint32_t* spl) {
+__device__ __forceinline__ void split_sample(const BlockSortLds& lds, gptr<const uint32_t> in, uint32_t n, uint32_t salt,
+                                             uint32_t* spl) {
   constexpr int THREADS = WAVES * 64, M = THREADS * SI;
   static_assert(M % B == 0, "whole sample steps per cell");
   static_assert(WAVES > 4, "the tile sort of up to 4 waves needs position words of its own");
@@ -56,8 +59,8 @@ __device__ __forceinline__ void split_sample(const BlockSortLds& lds, gptr<const
   const uint32_t stride = n / (uint32_t)M;
   uint32_t ks[SI];
 #pragma unroll
-  for (int j = 0; j < SI; ++j) ks[j] = in[sample_pos((uint32_t)(wid * 64 * SI + j * 64 + lane), stride)];
-  const uint32_t first = in[sample_pos(0u, stride)];
+  for (int j = 0; j < SI; ++j) ks[j] = in[sample_pos((uint32_t)(wid * 64 * SI + j * 64 + lane), stride, salt)];
+  const uint32_t first = in[sample_pos(0u, stride, salt)];
   const uint32_t diff = varying_bits<WAVES, SI>(ks, first, (uint32_t)M, lds.scan);
   const uint32_t low = diff >> 16 ? (1u << (16 - __builtin_clz(diff))) - 1u : 0u;  // below the 16 highest
 #pragma unroll 1
@@ -126,7 +129,7 @@ __device__ __forceinline__ CellMap split_map(const uint32_t* spl, uint16_t* lut,
 template <int WAVES, int IPT, int SI, int B, int RANK, bool KV>
 __global__ __launch_bounds__(WAVES * 64) void k_split(const uint32_t* __restrict__ in, const uint32_t* __restrict__ vin,
                                                      uint32_t* __restrict__ tmp, uint32_t* __restrict__ vtmp,
-                                                     uint32_t n, uint16_t* __restrict__ table,
+                                                     uint32_t n, uint32_t salt, uint16_t* __restrict__ table,
                                                      uint32_t* __restrict__ splitters) {
   constexpr int THREADS = WAVES * 64, T = THREADS * IPT;
   constexpr int CW = B > kBlockRadix ? B : kBlockRadix;
@@ -142,7 +145,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_split(const uint32_t* __restrict
   const uint32_t len = min(n - tbase, (uint32_t)T);
   const gptr<const uint32_t> gin = gmem(in);
   const BlockSortLds lds{s_stage, s_cnt, nullptr, s_scan, nullptr};
-  split_sample<WAVES, SI, B, RANK>(lds, gin, n, s_spl);
+  split_sample<WAVES, SI, B, RANK>(lds, gin, n, salt, s_spl);
   if (blockIdx.x == 0)
     for (int j = tid; j < B - 1; j += THREADS) splitters[j] = s_spl[j];
   uint32_t k[IPT], v[KV ? IPT : 1];
@@ -242,20 +245,24 @@ struct CellsLds {
 
 // A split array, as k_split left it.
 struct SplitArray {
-  const uint32_t* keys;
-  const uint32_t* vals;
+  uint32_t* keys;
+  uint32_t* vals;
   const uint16_t* table;
   uint32_t n, ntiles, tile, ncells;
 };
 
-// Where position i of the cell lies in the split array: the piece is the last one that starts at or
-// before i, found by halvings over the pieces' starts (lanes of neighbouring positions read the
-// same words).
-__device__ __forceinline__ uint32_t cell_src(const CellsLds& lds, uint32_t top, uint32_t i) {
-  uint32_t t = 0u;
-  for (uint32_t s = top; s > 0u; s >>= 1)
-    if (lds.poff[t + s] <= i) t += s;
-  return lds.psrc[t] + i;
+// The pieces that hold positions i[] of the cell: each is the last one that starts at or before its
+// position, found by halvings over the pieces' starts, all positions together so that their reads overlap
+// (lanes of neighbouring positions read the same words).  Position i lies at place psrc[piece] + i of the
+// split array.
+template <int U>
+__device__ __forceinline__ void cell_find(const CellsLds& lds, uint32_t top, const uint32_t (&i)[U], uint32_t (&piece)[U]) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) piece[u] = 0u;
+  for (uint32_t s = top; s > 0u; s >>= 1) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) piece[u] += lds.poff[piece[u] + s] <= i[u] ? s : 0u;
+  }
 }
 
 // The pieces of cell b: poff and psrc from the table's columns b and b+1; returns the cell's length
@@ -304,16 +311,12 @@ __device__ __forceinline__ uint32_t cell_sort_tile(const CellsLds& lds, const Sp
   }
   const gptr<const uint32_t> keys = gmem(a.keys), vals = gmem(a.vals);
   const uint32_t lb0 = (threadIdx.x >> 6) * (64u * I) + (threadIdx.x & 63u);
-  uint32_t k[I], v[KV ? I : 1], src[I];
+  uint32_t k[I], v[KV ? I : 1], at[I], src[I];
 #pragma unroll
-  for (int j = 0; j < I; ++j) src[j] = 0u;
-  // halvings of all the lane's positions together: their reads overlap
-  for (uint32_t s = top; s > 0u; s >>= 1) {
+  for (int j = 0; j < I; ++j) at[j] = lb0 + j * 64u;
+  cell_find<I>(lds, top, at, src);
 #pragma unroll
-    for (int j = 0; j < I; ++j) src[j] += lds.poff[src[j] + s] <= lb0 + j * 64u ? s : 0u;
-  }
-#pragma unroll
-  for (int j = 0; j < I; ++j) src[j] = lds.psrc[src[j]] + lb0 + j * 64u;
+  for (int j = 0; j < I; ++j) src[j] = lds.psrc[src[j]] + at[j];
 #pragma unroll
   for (int j = 0; j < I; ++j) k[j] = lb0 + j * 64u < len ? keys[src[j]] - lo : 0xFFFFFFFFu;
   if constexpr (KV) {
@@ -343,138 +346,148 @@ __device__ __forceinline__ void cell_fill(const CellsLds& lds, const SplitArray&
   }
   // four positions at a time: their searches and loads overlap
   for (uint32_t i = i0 + threadIdx.x; i < i1; i += 4u * THREADS) {
-    uint32_t src[4], val[4];
+    uint32_t at[4], src[4], val[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) src[u] = 0u;
-    for (uint32_t st = top; st > 0u; st >>= 1) {
+    for (int u = 0; u < 4; ++u) at[u] = i + u * THREADS;
+    cell_find<4>(lds, top, at, src);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) src[u] += lds.poff[src[u] + st] <= i + u * THREADS ? st : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) val[u] = i + u * THREADS < i1 ? vals[lds.psrc[src[u]] + i + u * THREADS] : 0u;
+    for (int u = 0; u < 4; ++u) val[u] = at[u] < i1 ? vals[lds.psrc[src[u]] + at[u]] : 0u;
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      if (i + u * THREADS < i1) {
-        out[i + u * THREADS] = key;
-        vout[i + u * THREADS] = val[u];
+      if (at[u] < i1) {
+        out[at[u]] = key;
+        vout[at[u]] = val[u];
       }
   }
 }
 
-// A cell longer than one tile whose keys differ (the sample missed the cell's keys): counted over 256
-// equal steps of its key range [lo, lo + range), then sorted tile by tile, each tile the longest run
-// of steps that fits, read out of the cell in its order; a step too long by itself is counted again
-// over finer steps, down to single values.  The cell is read once per count and per tile, and needs
-// no scratch: a cell of 10000 keys takes about 40 us.
+// A cell longer than one tile whose keys differ: two values that hold more than a tile between them, or keys
+// that the sample missed.  Sorted by stable sweeps, one per 8-bit digit that varies (key minus lo, so the
+// digits above the cell's range are constant): bucket counts of all digits in one sweep, then every sweep
+// ranks tile by tile and writes to the buckets' places.  The sweeps go from the cell's pieces to its part of
+// the output and back; an even number of them ends with a copy.  One workgroup does it all, so a long cell
+// sets the time of the sort, but every key is read at most six times: a cell of 100K keys takes 0.5 ms, one
+// of 9 * 2^17 (keys chosen off the salted positions) 6.6 ms; reading the cell twice for every tile of its
+// output, as before, took 455 ms.
 template <int WAVES, int IPT, int RANK, bool KV>
 __device__ __forceinline__ void cell_sort_oversize(const CellsLds& lds, const SplitArray& a, uint32_t* out_p, uint32_t* vout_p,
-                                   uint32_t top, uint32_t len, uint32_t lo, uint64_t range) {
-  constexpr uint32_t THREADS = WAVES * 64, CAP = THREADS * IPT;
-  constexpr int U = 4;  // keys per thread and step: their searches and loads overlap
+                                                   uint32_t top, uint32_t len, uint32_t lo) {
+  constexpr int R = kBlockRadix, D = 4, U = 4;
+  constexpr int I = 12;  // keys per lane; with all IPT of them the ballot rank spills
+  constexpr uint32_t THREADS = WAVES * 64, T = THREADS * I, COPIES = 4, CS = D * R + 1;
+  static_assert(2048u + COPIES * CS <= THREADS * IPT, "the tables share the stage");
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6;
-  const gptr<const uint32_t> keys = gmem(a.keys), vals = gmem(a.vals);
-  const gptr<uint32_t> out = gmem(out_p), vout = gmem(vout_p);
-  uint32_t* const h = lds.sort.cnt;         // 256 counts, [256] steps taken, [257] their keys
-  uint32_t* const part = lds.sort.cnt + 512;  // [U * WAVES] keys found by each wave and slot
-  uint64_t cur = 0u, end = range;  // key range still to sort, relative to lo; counted up to end
-  uint32_t done = 0u;
-  auto load = [&](uint32_t i0, uint32_t (&key)[U], uint32_t* val) {
-    uint32_t src[U];
+  const gptr<uint32_t> keys = gmem(a.keys), vals = gmem(a.vals), out = gmem(out_p), vout = gmem(vout_p);
+  uint32_t* const first = lds.sort.stage;          // [D * R] first position of every bucket
+  uint32_t* const running = lds.sort.stage + 1024;  // [R] next free position of every bucket
+  uint32_t* const lbase = lds.sort.stage + 1280;    // [R + 1] bucket starts in the tile
+  uint32_t* const count = lds.sort.stage + 2048;    // [COPIES * CS]
+  uint32_t* const cnt = lds.sort.cnt + wid * R;     // the wave's bucket counts
+  __syncthreads();
+  for (uint32_t i = tid; i < COPIES * CS; i += THREADS) count[i] = 0u;
+  __syncthreads();
+  uint32_t* const mine = count + (lane % COPIES) * CS;
+  for (uint32_t i0 = 0u; i0 < len; i0 += U * THREADS) {
+    uint32_t at[U], src[U], key[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) src[u] = 0u;
-    for (uint32_t st = top; st > 0u; st >>= 1) {
+    for (int u = 0; u < U; ++u) at[u] = i0 + u * THREADS + tid;
+    cell_find<U>(lds, top, at, src);
 #pragma unroll
-      for (int u = 0; u < U; ++u) src[u] += lds.poff[src[u] + st] <= i0 + u * THREADS + tid ? st : 0u;
-    }
+    for (int u = 0; u < U; ++u) key[u] = at[u] < len ? keys[lds.psrc[src[u]] + at[u]] - lo : 0u;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t i = i0 + u * THREADS + tid, at = lds.psrc[src[u]] + i;
-      key[u] = i < len ? keys[at] - lo : 0xFFFFFFFFu;
-      if (KV && val) val[u] = i < len ? vals[at] : 0u;
-    }
-  };
-  while (done < len) {
-    int sh = 0;
-    while (((end - cur - 1u) >> sh) > 255u) ++sh;
-    __syncthreads();
-    for (uint32_t i = tid; i < 256u; i += THREADS) h[i] = 0u;
-    __syncthreads();
-    for (uint32_t i0 = 0u; i0 < len; i0 += U * THREADS) {
-      uint32_t key[U];
-      load(i0, key, nullptr);
+    for (int u = 0; u < U; ++u)
+      if (at[u] < len) {
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (i0 + u * THREADS + tid < len && key[u] >= cur && key[u] < end) atomicAdd(&h[(uint32_t)((key[u] - cur) >> sh)], 1u);
-    }
-    __syncthreads();
-    if (tid == 0u) {
-      uint32_t st = 0u, c = 0u;
-      while (st < 256u && c + h[st] <= CAP) c += h[st++];
-      if (st == 0u && sh == 0) { c = h[0]; st = 1u; }  // one value: copied, not sorted
-      h[256] = st;
-      h[257] = c;
-    }
-    __syncthreads();
-    const uint32_t steps = h[256], cnt = h[257];
-    if (steps == 0u) {  // the first step alone is too long
-      end = cur + (1ull << sh);
-      continue;
-    }
-    const uint64_t stop = cur + ((uint64_t)steps << sh);
-    const bool copy = cnt > CAP;
-    // the keys in [cur, stop), in the cell's order: into the stage, or one value straight out
-    uint32_t at = 0u;
-    for (uint32_t i0 = 0u; i0 < len; i0 += U * THREADS) {
-      uint32_t key[U], val[U];
-      load(i0, key, val);
-      uint64_t m[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        m[u] = __builtin_amdgcn_ballot_w64(i0 + u * THREADS + tid < len && key[u] >= cur && key[u] < stop);
-      __syncthreads();
-      if (lane == 0u) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) part[u * WAVES + wid] = (uint32_t)__popcll(m[u]);
+        for (int d = 0; d < D; ++d) atomicAdd(&mine[d * R + ((key[u] >> (8 * d)) & (R - 1))], 1u);
       }
-      __syncthreads();
+  }
+  __syncthreads();
+  uint32_t varies = 0u;  // digits of which no bucket holds every key
+  for (uint32_t i = tid; i < D * R; i += THREADS) {
+    uint32_t c = 0u;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        uint32_t p = at + lanes_below(m[u]);
-        for (uint32_t w = 0; w < (uint32_t)WAVES; ++w) {
-          const uint32_t c = part[u * WAVES + w];
-          p += w < wid ? c : 0u;
-          at += c;
+    for (uint32_t q = 0; q < COPIES; ++q) c += count[q * CS + i];
+    first[i] = c;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    if (!__syncthreads_or(tid < (uint32_t)R && first[d * R + tid] == len)) varies |= 1u << d;
+    lds_exclusive_scan<R, (int)THREADS>(first + d * R, lds.sort.scan);
+  }
+  const uint32_t lb0 = wid * (64u * I) + lane;
+  bool in_out = false;  // where the keys are
+#pragma unroll 1
+  for (uint32_t left = varies; left; left &= left - 1u) {
+    const int d = __builtin_ctz(left), shift = 8 * d;
+    for (uint32_t b = tid; b < (uint32_t)R; b += THREADS) running[b] = first[d * R + b];
+#pragma unroll 1
+    for (uint32_t t0 = 0u; t0 < len; t0 += T) {
+      uint32_t k[I], v[KV ? I : 1], r[I], at[I], piece[I];
+#pragma unroll
+      for (int j = 0; j < I; ++j) at[j] = t0 + lb0 + j * 64u;
+      if (in_out) {
+#pragma unroll
+        for (int j = 0; j < I; ++j) k[j] = at[j] < len ? out[at[j]] - lo : 0xFFFFFFFFu;
+        if constexpr (KV) {
+#pragma unroll
+          for (int j = 0; j < I; ++j) v[j] = at[j] < len ? vout[at[j]] : 0u;
         }
-        if (!((m[u] >> lane) & 1u)) continue;
-        if (copy) {
-          out[done + p] = key[u] + lo;
-          if constexpr (KV) vout[done + p] = val[u];
-        } else {
-          lds.sort.stage[p] = key[u];
-          if constexpr (KV) lds.sort.vstage[p] = val[u];
+      } else {
+        cell_find<I>(lds, top, at, piece);
+#pragma unroll
+        for (int j = 0; j < I; ++j) piece[j] = lds.psrc[piece[j]] + at[j];
+#pragma unroll
+        for (int j = 0; j < I; ++j) k[j] = at[j] < len ? keys[piece[j]] - lo : 0xFFFFFFFFu;
+        if constexpr (KV) {
+#pragma unroll
+          for (int j = 0; j < I; ++j) v[j] = at[j] < len ? vals[piece[j]] : 0u;
         }
       }
-    }
-    __syncthreads();
-    if (!copy) {
-      const uint32_t lb0 = wid * (64u * IPT) + lane;
-      uint32_t k[IPT], v[KV ? IPT : 1];
+      for (uint32_t b = lane; b < (uint32_t)R; b += 64u) cnt[b] = 0u;
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int j = 0; j < IPT; ++j) {
-        k[j] = lb0 + j * 64u < cnt ? lds.sort.stage[lb0 + j * 64u] : 0xFFFFFFFFu;
-        if constexpr (KV) v[j] = lb0 + j * 64u < cnt ? lds.sort.vstage[lb0 + j * 64u] : 0u;
+      for (int j = 0; j < I; ++j) {
+        const uint32_t b = (k[j] >> shift) & (R - 1);
+        if constexpr (RANK == SEG_RANK_ATOMIC) r[j] = rank_slot(cnt, b);
+        else r[j] = rank_ballot<kBlockBits>(cnt, b);
       }
-      block_sort_impl<WAVES, IPT, RANK, KV>(lds.sort, k, v, varying_bits<WAVES, IPT>(k, 0u, cnt, lds.sort.scan));
+      tile_bucket_offsets<R, WAVES>(lds.sort.cnt, lbase, lds.sort.scan);
 #pragma unroll
-      for (int j = 0; j < IPT; ++j)
-        if (lb0 + j * 64u < cnt) {
-          out[done + lb0 + j * 64u] = k[j] + lo;
-          if constexpr (KV) vout[done + lb0 + j * 64u] = v[j];
+      for (int j = 0; j < I; ++j) {
+        const uint32_t b = (k[j] >> shift) & (R - 1);
+        r[j] += running[b] + cnt[b] - lbase[b];  // the key's position in the cell
+      }
+      if (in_out) {
+        cell_find<I>(lds, top, r, piece);
+#pragma unroll
+        for (int j = 0; j < I; ++j) r[j] += lds.psrc[piece[j]];
+      }
+      const gptr<uint32_t> to = in_out ? keys : out, vto = in_out ? vals : vout;
+#pragma unroll
+      for (int j = 0; j < I; ++j)
+        if (at[j] < len) {
+          to[r[j]] = k[j] + lo;
+          if constexpr (KV) vto[r[j]] = v[j];
         }
+      __syncthreads();  // the buckets' places and counts are read
+      for (uint32_t b = tid; b < (uint32_t)R; b += THREADS) running[b] += lbase[b + 1u] - lbase[b];
     }
-    done += cnt;
-    cur = stop;
-    end = range;
+    in_out = !in_out;
+    __syncthreads();  // this sweep's writes before the next one's reads
+  }
+  if (in_out) return;
+  for (uint32_t i0 = 0u; i0 < len; i0 += U * THREADS) {
+    uint32_t at[U], src[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) at[u] = i0 + u * THREADS + tid;
+    cell_find<U>(lds, top, at, src);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (at[u] < len) {
+        out[at[u]] = keys[lds.psrc[src[u]] + at[u]];
+        if constexpr (KV) vout[at[u]] = vals[lds.psrc[src[u]] + at[u]];
+      }
   }
 }
 
@@ -513,9 +526,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void k_cells(SplitArray a, uint32_t*
     const gptr<uint32_t> o = gmem(out) + base, vo = gmem(vout) + (KV ? base : 0u);
     if (equal) cell_fill<THREADS, KV>(lds, a, o, vo, top, 0u, len, lo);
     else if (len <= CAP) diff = cell_sort_tile<WAVES, IPT, RANK, KV>(lds, a, o, vo, top, len, lo);
-    else
-      cell_sort_oversize<WAVES, IPT, RANK, KV>(lds, a, out + base, KV ? vout + base : nullptr, top, len, lo,
-                                               (b < nspl ? (uint64_t)spl[b] + 1u : 1ull << 32) - lo);
+    else cell_sort_oversize<WAVES, IPT, RANK, KV>(lds, a, out + base, KV ? vout + base : nullptr, top, len, lo);
   }
   // splitters of the output contract whose positions lie in this cell, from LDS (of an oversize cell
   // from memory); the last cell writes those of the empty cells past the end

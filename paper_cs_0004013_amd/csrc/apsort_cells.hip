@@ -60,17 +60,26 @@ size_t cells_table_bytes(size_t n, bool pairs) {
   return up256c(sizeof(uint32_t) * c.cells) + up256c(sizeof(uint16_t) * c.cells * ((n + c.tile - 1) / c.tile));
 }
 
+// Salt of the sample's positions: the input's address, mixed (the finalizer of SplitMix64).
+static uint32_t sample_salt(const void* in) {
+  uint64_t x = (uint64_t)(uintptr_t)in;
+  x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+  x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+  return (uint32_t)(x >> 32);
+}
+
 template <int IPT, int SI, int B, bool KV>
 static void launch_split(hipStream_t s, const uint32_t* in, const uint32_t* vin, uint32_t* tmp, uint32_t* vtmp, uint32_t n,
                          uint16_t* table, uint32_t* spl) {
   constexpr uint32_t T = 512 * IPT;
   const dim3 grid((n + T - 1) / T);
+  const uint32_t salt = sample_salt(in);
   if (lane_order_ok())
-    hipLaunchKernelGGL((k_split<8, IPT, SI, B, SEG_RANK_ATOMIC, KV>), grid, dim3(512), 0, s, in, vin, tmp, vtmp, n, table,
-                       spl);
+    hipLaunchKernelGGL((k_split<8, IPT, SI, B, SEG_RANK_ATOMIC, KV>), grid, dim3(512), 0, s, in, vin, tmp, vtmp, n, salt,
+                       table, spl);
   else
-    hipLaunchKernelGGL((k_split<8, IPT, SI, B, SEG_RANK_BALLOT, KV>), grid, dim3(512), 0, s, in, vin, tmp, vtmp, n, table,
-                       spl);
+    hipLaunchKernelGGL((k_split<8, IPT, SI, B, SEG_RANK_BALLOT, KV>), grid, dim3(512), 0, s, in, vin, tmp, vtmp, n, salt,
+                       table, spl);
 }
 
 template <bool KV>
