@@ -3,13 +3,17 @@ workgroup, keys per lane) of each length group by measurement.
 
 The length groups are fixed ranges of length classes ceil(log2(segment length)), one per tile
 size: more than 8K keys (16K-key tiles, longer segments by digit sweeps), (4K, 8K], (2K, 4K] and
-up to 2K.  A batch's segments of up to 4096 keys have a kernel of their own, so the choice for the last
-two groups matters only to batched server requests and stays within the noise here.  Every group is one more concurrent persistent kernel: classes that run the same
+up to 2K.  Every group is one more concurrent persistent kernel: classes that run the same
 configuration are better served by one group (a fifth group splitting off the segments above 16K
-measured 1.5-2% slower with the same configurations).  The tuning batch has the workload's shape: 4096 segments with lengths
-log-uniform in [64, 2^18] and distributions (a)-(e) by segment seed; three such batches are
-drawn with seeds of their own (not the benchmark's), because which configuration wins depends on
-the particular lengths (the longest segments set the critical path).  The groups are tuned by
+measured 1.5-2% slower with the same configurations).  A batch's segments of up to 4096 keys have
+a kernel of their own, whatever the table: the last two groups serve batched server requests alone.
+No choice for them changes a tuning run's time, so they are not tuned and keep the built-in
+configurations (which won when these groups still sorted a batch's short segments).
+
+The tuning batch has the workload's shape: 4096 segments with lengths log-uniform in [64, 2^18] and
+distributions (a)-(e) by segment seed; three such batches are drawn with seeds of their own (not the
+benchmark's), because which configuration wins depends on the particular lengths (the longest
+segments set the critical path).  The other groups are tuned by
 coordinate descent: for one group at a time, every compiled-in configuration is tried with the
 other groups' choices fixed, scored by the sum over the batches of the median of `reps` runs
 (input restored before each run, HIP events on the sort's stream); the lowest score is kept, and
@@ -33,6 +37,7 @@ DEFAULT_TABLE = os.path.join(HERE, "tune_gfx950.txt")
 GROUPS = [(14, 31), (13, 13), (12, 12), (1, 11)]   # > 8K, (4K, 8K], (2K, 4K], <= 2K keys
 START = [10, 0, 5, 3]                               # configurations the descent starts from (the built-in table)
 TUNE_SEEDS = (7919, 104729, 1299709)
+TILE_CLASS = 12    # segments of the classes up to this one have a kernel of their own in a batch
 
 
 def _batch(seed: int):
@@ -40,6 +45,30 @@ def _batch(seed: int):
     L = inputs.segment_lengths(4096, seed=seed)
     keys, off, _ = inputs.segment_keys(L)
     return keys, off
+
+
+def descend(measure, ncfg: int, rounds: int, report=lambda text: None) -> list[int]:
+    """Coordinate descent from START: the configuration of each group by measure(choice), in ms."""
+    choice = list(START)
+    best = measure(choice)
+    report(f"start {choice}: {best:.3f} ms")
+    for rnd in range(rounds):
+        for g, (lo, hi) in enumerate(GROUPS):
+            if hi <= TILE_CLASS:
+                continue
+            for cfg in range(ncfg):
+                if cfg == choice[g]:
+                    continue
+                prev = choice[g]
+                choice[g] = cfg
+                ms = measure(choice)
+                report(f"round {rnd} group {g} classes {lo}..{hi} cfg {cfg}: {ms:.3f} ms")
+                if ms < best * 0.995:
+                    best = ms
+                else:
+                    choice[g] = prev
+        report(f"after round {rnd}: {choice} {best:.3f} ms")
+    return choice
 
 
 def tune(reps: int = 5, rounds: int = 2, out: str | None = DEFAULT_TABLE, verbose: bool = True):
@@ -53,14 +82,18 @@ def tune(reps: int = 5, rounds: int = 2, out: str | None = DEFAULT_TABLE, verbos
     stream = torch.cuda.Stream()
     batches = [_batch(sd) for sd in TUNE_SEEDS]
     nkeys = sum(int(k.size) for k, _ in batches)
-    choice = list(START)
+
+    def report(text: str) -> None:
+        if verbose:
+            print(f"[tune] {text}", flush=True)
+
     try:
         with torch.cuda.stream(stream):
             dev = [(torch.from_numpy(k.view(np.int32)).to("cuda"), torch.from_numpy(o.view(np.int32)).to("cuda"))
                    for k, o in batches]
             t_work = torch.empty(max(int(k.size) for k, _ in batches), dtype=torch.int32, device="cuda")
 
-            def measure() -> float:
+            def measure(choice: list[int]) -> float:
                 binding.set_segmented_groups([(lo, hi, c) for (lo, hi), c in zip(GROUPS, choice)])
                 total = 0.0
                 for t_src, t_off in dev:
@@ -79,29 +112,9 @@ def tune(reps: int = 5, rounds: int = 2, out: str | None = DEFAULT_TABLE, verbos
                     total += float(np.median(times))
                 return total
 
-            best = measure()
-            if verbose:
-                print(f"[tune] {len(dev)} batches of 4096 segments, {nkeys} keys; start {choice}: {best:.3f} ms",
-                      flush=True)
-            for rnd in range(rounds):
-                for g in range(len(GROUPS)):
-                    for cfg in range(ncfg):
-                        if cfg == choice[g]:
-                            continue
-                        prev = choice[g]
-                        choice[g] = cfg
-                        ms = measure()
-                        if verbose:
-                            bits, waves, ipt = binding.ap_segmented_config_info(cfg)
-                            print(f"[tune] round {rnd} group {g} classes {GROUPS[g][0]}..{GROUPS[g][1]} cfg {cfg} "
-                                  f"(bits {bits}, waves {waves}, ipt {ipt}): {ms:.3f} ms", flush=True)
-                        if ms < best * 0.995:
-                            best = ms
-                        else:
-                            choice[g] = prev
-                if verbose:
-                    print(f"[tune] after round {rnd}: {choice} {best:.3f} ms "
-                          f"({nkeys / best / 1e6:.1f} Gkeys/s)", flush=True)
+            report(f"{len(dev)} batches of 4096 segments, {nkeys} keys; configurations (digit bits, waves, keys "
+                   f"per lane): {[binding.ap_segmented_config_info(c) for c in range(ncfg)]}")
+            choice = descend(measure, ncfg, rounds, report)
     finally:
         binding.set_segmented_groups(saved)
     chosen = [(lo, hi, c) for (lo, hi), c in zip(GROUPS, choice)]
