@@ -462,8 +462,9 @@ ap_status ap_set_rank_mode(int mode);
 /*
  * ap_debug_pass -- debug mode of the device-wide digit pass (Sec. 3.2 partial
  * sort and distribution of one digit), process-wide, for the keys-only passes
- * of ap_sort_u32, ap_sort_u32_ws, ap_sort_u32_noalloc and ap_sort_u32_msd.
- * The passes then run a separate kernel; the default kernels are not changed.
+ * of ap_sort_u32, ap_sort_u32_ws, ap_sort_u32_noalloc and ap_sort_u32_msd
+ * (of ap_sort_u32 above 16384 keys).  The passes then run a separate kernel, at
+ * every size that has passes to run; the default kernels are not changed.
  *   mode 0: off (default).
  *   mode 1: timing perturbation.  Every tile sleeps, with probability 1/2 per
  *     point and for 0 - 12 us drawn from SplitMix64(seed, tile, digit, point),
@@ -478,8 +479,9 @@ ap_status ap_set_rank_mode(int mode);
  *     claimed, ranked, scanned, reordered, looked back and scattered (stores
  *     complete); words 6 and 7 are not written.  The trace kernel adds
  *     barriers after the rank and the reorder and waits for its stores, so a
- *     traced pass runs slightly slower.  d_trace must stay valid while sorts
- *     run in this mode.
+ *     traced pass runs slightly slower.  A trace is taken with 32K-key tiles
+ *     where the sort would take 20K, 24K or 28K.  d_trace must stay valid while
+ *     sorts run in this mode.
  * Errors: AP_ERR_INVALID (mode outside 0..2; mode 2 without a buffer).
  */
 ap_status ap_debug_pass(int mode, uint64_t seed, unsigned long long *d_trace, size_t trace_records);
@@ -488,9 +490,11 @@ ap_status ap_debug_pass(int mode, uint64_t seed, unsigned long long *d_trace, si
  * Tile shape of the device-wide digit pass (Sec. 3.2 partial sort and
  * distribution, one digit of the LSD sort of Sec. 3.3.1).  By default the
  * tile (one workgroup of 16 waves) grows with the array: 4K keys below 2^17,
- * 8K below 2^20, 16K below 2^22, 32K from there on (the mask rank uses 16K
- * where 32K is chosen; key-value pairs use at most 8K below 2^22 and 16K from
- * there on).
+ * 8K below 2^20, 16K below 2^22, and from there on the smallest of 20K, 24K,
+ * 28K and 32K that needs no more rounds of tiles on the device's CUs than 32K
+ * does (the mask rank uses 16K there; key-value pairs use at most 8K below
+ * 2^22 and 16K from there on).  Arrays short enough for the sorts of one or
+ * two launches run these passes only if a shape is forced.
  * shape: -1 = by size (default), 0..3 = always 4K, 8K, 16K, 32K keys (pairs:
  * at most 16K).
  * Process-wide, for tests and tuning; results do not depend on it.  A

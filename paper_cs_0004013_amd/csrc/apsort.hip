@@ -322,6 +322,9 @@ static void launch_pass_dbg_mode(bool atomic_rank, dim3 grid, hipStream_t s, con
   hipLaunchKernelGGL((k_pass_dbg<kBits, W, I, RANK_ATOMIC, DBG>), grid, dim3(W * 64), 0, s, in, out, tmp, n, d, plan,
                      base_d, st_d, tctr, a);
 }
+// The perturbed pass runs whatever tile the sort runs.  The trace is built for the four tiles that
+// ap_set_pass_shape names (a reader of its records has to know the tile): it takes 32K keys for the tiles between.
+static constexpr bool trace_shape(int ipt) { return (ipt & (ipt - 1)) == 0; }
 template <int W, int I>
 static void launch_pass_dbg(const PassDebugState& st, bool atomic_rank, dim3 grid, hipStream_t s, const uint32_t* in,
                             uint32_t* out, uint32_t* tmp, uint32_t n, int d, uint32_t ntiles, const uint32_t* plan,
@@ -331,10 +334,13 @@ static void launch_pass_dbg(const PassDebugState& st, bool atomic_rank, dim3 gri
   a.trace = st.trace;
   a.trace_records = st.trace_records;
   a.record0 = (uint32_t)d * ntiles;
-  if (st.mode == PASS_DBG_PERTURB)
-    launch_pass_dbg_mode<W, I, PASS_DBG_PERTURB>(atomic_rank, grid, s, in, out, tmp, n, d, plan, base_d, st_d, tctr, a);
-  else
-    launch_pass_dbg_mode<W, I, PASS_DBG_TRACE>(atomic_rank, grid, s, in, out, tmp, n, d, plan, base_d, st_d, tctr, a);
+  if constexpr (trace_shape(I)) {
+    if (st.mode == PASS_DBG_TRACE) {
+      launch_pass_dbg_mode<W, I, PASS_DBG_TRACE>(atomic_rank, grid, s, in, out, tmp, n, d, plan, base_d, st_d, tctr, a);
+      return;
+    }
+  }
+  launch_pass_dbg_mode<W, I, PASS_DBG_PERTURB>(atomic_rank, grid, s, in, out, tmp, n, d, plan, base_d, st_d, tctr, a);
 }
 
 // ---------------------------------------------------------------- launch sequence
@@ -373,7 +379,7 @@ ap_status enqueue_sort_parts(const uint32_t* d_in, uint32_t* d_out, size_t n, in
     if (cells_sort_size(n, pairs)) return enqueue_cells(d_in, d_out, d_vin, d_vout, n, P, d_spl, status, tmp, vtmp, s);
   }
   int sh = pairs ? std::min(shape_for_pairs(n), shape_used(n, atomic_rank)) : shape_used(n, atomic_rank);
-  if (!pairs && sh > 3 && dbg.mode != PASS_DBG_NONE) sh = 3;  // the debug kernels are built for four shapes
+  if (!pairs && dbg.mode == PASS_DBG_TRACE && !trace_shape(kShapes[sh].ipt)) sh = 3;
   const int T = tile_keys(sh);
   const uint32_t ntiles = (uint32_t)((n + T - 1) / T);
   if (ntiles > L.ntiles) return fail(AP_ERR_INVALID, "workspace sized for a larger tile (shape changed after sizing)");
@@ -419,18 +425,9 @@ ap_status enqueue_sort_parts(const uint32_t* d_in, uint32_t* d_out, size_t n, in
     } else {
       switch (sh) {
         case 3: APS_PASS(16, 32, false); break;
-        case 4:
-          launch_pass<16, 20, false, false>(true, grid, s, d_in, d_out, tmp, nn, d, plan, base_d, st_d, tctr, d_vin, d_vout,
-                                            vtmp);
-          break;
-        case 5:
-          launch_pass<16, 24, false, false>(true, grid, s, d_in, d_out, tmp, nn, d, plan, base_d, st_d, tctr, d_vin, d_vout,
-                                            vtmp);
-          break;
-        case 6:
-          launch_pass<16, 28, false, false>(true, grid, s, d_in, d_out, tmp, nn, d, plan, base_d, st_d, tctr, d_vin, d_vout,
-                                            vtmp);
-          break;
+        case 4: APS_PASS(16, 20, false); break;
+        case 5: APS_PASS(16, 24, false); break;
+        case 6: APS_PASS(16, 28, false); break;
         case 2: APS_PASS(16, 16, false); break;
         case 1: APS_PASS(16, 8, false); break;
         default: APS_PASS(16, 4, false); break;
