@@ -262,7 +262,8 @@ ap_status ap_sort_u32_segmented(uint32_t *d_keys, size_t n_total,
 /*
  * ap_segmented_set_long_min / ap_segmented_get_long_min -- segments of at
  * least long_min keys are sorted by the device-wide passes (0 = never; 1 is
- * AP_ERR_INVALID).  Process-wide; results do not depend on it.
+ * AP_ERR_INVALID; values up to 4096 act as 4097, shorter segments have a kernel
+ * of their own).  Process-wide; results do not depend on it.
  */
 ap_status ap_segmented_set_long_min(size_t long_min);
 size_t ap_segmented_get_long_min(void);

@@ -241,6 +241,8 @@ struct SegLayout {
 static size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 static SegLayout seg_layout(size_t n_total, int nseg, size_t long_min) {
   SegLayout L{};
+  // k_seg_tiles sorts every segment of up to kSegTileMax keys: a lower threshold means the first length past that
+  if (long_min >= 2) long_min = std::max(long_min, (size_t)kSegTileMax + 1);
   const bool longs = long_min >= 2 && long_min <= n_total;
   L.long_min = longs ? (uint32_t)long_min : 0xFFFFFFFFu;
   L.nlong_max = longs ? (uint32_t)(n_total / long_min) : 0u;
