@@ -370,7 +370,7 @@ ap_status enqueue_sort_parts(const uint32_t* d_in, uint32_t* d_out, size_t n, in
   const int inplace = (d_in == d_out) ? 1 : 0;
   const bool atomic_rank = lane_order_ok();
   const PassDebugState dbg = pass_debug();
-  // Short arrays take one workgroup, middling ones the two-launch sort, unless the digit passes are
+  // Short arrays take one launch, middling ones the two-launch sort, unless the digit passes are
   // asked for (a forced tile shape, a debug mode of the pass, the bucketing variant's digits).
   if (first_digit == 0 && g_shape_override.load() < 0 && dbg.mode == PASS_DBG_NONE) {
     if (small_sort_size(n, pairs))
@@ -686,8 +686,8 @@ ap_status ap_sort_u32(const uint32_t* d_in, uint32_t* d_out, size_t n, int P, ui
   if (st != AP_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (n == 0) return sort_with_ws(d_in, d_out, 0, P, d_splitters, nullptr, 0, s);
-  // A short array is sorted in one launch by one workgroup and needs no workspace (unless a pass
-  // shape is forced, which pins the device-wide kernels at every size).
+  // A short array is sorted in one launch and needs no workspace (unless a pass shape is forced, which
+  // pins the device-wide kernels at every size).
   if (n <= kSmallSortMax && g_shape_override.load() < 0) {
     st = check_lane_order(s);
     if (st != AP_OK) return st;

@@ -19,6 +19,12 @@ namespace aps {
 //    100K   4 / 128 19.9, 4 / 256 17.8, 8 / 256 18.3
 //    300K   4 / 256 25.3, 8 / 512 21.5
 //      1M   8 / 512 35.8, 16 / 512 34.1 (16 waves of 8 keys: 35.5)
+// and the two shapes at each bound, mean over ten arrays, uniform / Gaussian keys (pairs alike):
+//    48K   4 / 128 16.3 / 16.6, 4 / 256 16.1 / 16.6
+//    200K   4 / 256 19.9 / 21.1, 8 / 512 20.3 / 22.2; at 260K 22.0 / 22.4 and 21.2 / 23.6
+//    400K   8 / 512 with 4 sample keys per cell 23.4 / 25.3, 16 / 512 25.2 / 28.1; at 500K 24.8 / 28.2
+//           and 26.4 / 29.7: by time the line could lie higher, but the cells are then longer for as few
+//           sample keys, and nearer to k_cells' tile
 struct CellShape {
   size_t max_n;
   uint32_t tile, cells, sample;
@@ -29,12 +35,12 @@ constexpr CellShape kCellShapes[] = {
     {(size_t)400000, 4096, 512, 2048},
     {(size_t)9 << 17, 8192, 512, 4096},
 };
-// Above these the longest cells come near their tile (8 sample keys per cell and 4 times the mean
-// length of room: one cell in 10^7 longer): the digit passes take over.  At 5 * 2^18 keys of 256
-// values a cell of two values did not fit, and the sort took 166 us instead of 33.
-// Pairs stop earlier: the digit passes skip what few-valued keys have in common, and above the bound
-// they sort constant or byte-valued keys faster (600K pairs: uniform 58 -> 39 us, byte values
-// 30.0 -> 30.6, constant 22.6 -> 24.5; 983K: 66 -> 48, 32.4 -> 35.4, 23.5 -> 28.0).
+// Above these the digit passes take over.  The longest cells come near their tile there (8 sample keys per
+// cell and 4 times the mean length of room: one cell in 10^7 longer), and the digit passes skip what
+// few-valued keys have in common.  Digit passes / two launches, us: 9 * 2^17 + 1 keys uniform 59.6 / 37.8,
+// constant 22.2 / 22.7, bytes 30.0 / 29.8; 5 * 2^18 keys 60.7 / 42.1, 22.0 / 23.1, 30.4 / 30.2.
+// Pairs stop earlier: 10 * 2^16 + 1 uniform 57.4 / 36.4, constant 22.0 / 21.3, bytes 29.0 / 26.8, log-uniform
+// 51.6 / 52.2; 800K 60.5 / 37.4, 22.0 / 22.5, 29.5 / 29.5, 53.7 / 59.2.
 constexpr size_t kCellsMax = (size_t)9 << 17, kCellsMaxPairs = (size_t)10 << 16;
 constexpr int kCellIpt = 20, kCellIptPairs = 16;
 constexpr uint32_t kPairsSmallMax = 8192;

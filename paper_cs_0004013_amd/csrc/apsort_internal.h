@@ -71,7 +71,7 @@ ap_status enqueue_sort_parts(const uint32_t* d_in, uint32_t* d_out, size_t n, in
                              void* scratch, const Layout& L, hipStream_t s, const uint32_t* d_vin = nullptr,
                              uint32_t* d_vout = nullptr, int first_digit = 0);
 ap_status cached_workspace(size_t need, hipStream_t s, void** out);
-// Arrays of at most kSmallSortMax keys: sorted in one launch by one workgroup (apsort_seg.hip).
+// Arrays of at most kSmallSortMax keys: sorted in one launch (apsort_seg.hip).
 constexpr uint32_t kSmallSortMax = 16384;
 ap_status enqueue_small_sort(const uint32_t* d_in, uint32_t* d_out, size_t n, int P, uint32_t* d_spl,
                              hipStream_t s);

@@ -4,10 +4,11 @@
 // segmented-sort control block, the descriptor array, and the device-wide sort's control words,
 // which are zeroed once and left zero by every sort).  Scratch comes from one arena of the
 // memory budget, shared by the slots through the core's ledger.  A batch of short requests
-// becomes one launch of the persistent segmented kernel over host-built descriptors (longest
-// first), each descriptor pointing at the caller's input and output buffers directly, so no key is
-// copied in or out.  A long request runs alone through the device-wide sort with its reserved
-// range of the arena as its workspace.
+// becomes one launch of the persistent segmented kernel per length group over host-built descriptors
+// (longest first), each descriptor pointing at the caller's input and output buffers directly, so no key is
+// copied in or out; a batch of one request of at most 16384 keys is one launch of the single-array sort.
+// A long request runs alone through the single-array sort of its length (two launches up to 9 * 2^17 keys,
+// the device-wide passes above) with its reserved range of the arena as its workspace.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -96,7 +97,7 @@ class HipExecutor : public srv::Executor {
   ap_status launch_batch(int slot, std::vector<srv::Request*>& reqs, size_t scratch_off, size_t) override {
     ApRange range("ap_server batch");
     SlotRes& sl = slots_[slot];
-    // A batch of one request short enough for one workgroup (what a lightly loaded server forms):
+    // A batch of one request short enough for one launch (what a lightly loaded server forms):
     // the single-array sort's one launch, with no descriptor upload.
     if (reqs.size() == 1 && reqs[0]->n >= 1 && reqs[0]->n <= kSmallSortMax) {
       srv::Request* r = reqs[0];
