@@ -60,7 +60,7 @@ __device__ uint32_t merge_split_group(const uint32_t* __restrict__ a, const uint
 // splits[t] = split(min(t * T, n)) for t < nsplits; a workgroup finds TILES of them.  First its two waves
 // find the ends of its window, the splits of its first boundary and of the next workgroup's; split() is
 // monotone in the diagonal, so a group of lanes then finds each boundary inside the window.  One launch:
-// windows found by a launch of their own cost 6.8 of 94.4 us for 30.0M + 29.8M keys (now 91.4), and the launches
+// windows found by a launch of their own cost 6.8 of 94.4 us for 36.7M + 23.1M keys (now 91.4), and the launches
 // are most of a short merge (2 x 64K keys 11.2 -> 9.4 us).  Bound by the round trips
 // to memory and by the lines the candidates pull in: 16 waves, fewer round trips, take 109 us.
 constexpr uint32_t kPartThreads = 128;
