@@ -79,13 +79,15 @@ def test_keys_off_the_known_positions_cost_no_more(n, pairs):
 
 
 # what the unseen keys vary in: a cell of one value, two values, and one to four digits (odd and even
-# numbers of sweeps), the last with the type's largest key
+# numbers of sweeps), also with the type's largest key
 def _unseen(full: np.ndarray, kind: str) -> np.ndarray:
     base = np.uint32(0x70000000)
     if kind == "value":
         return np.full(full.size, base + np.uint32(1), np.uint32)
     if kind == "two_values":
         return base + (full & np.uint32(1)) * np.uint32(0x10001)
+    if kind == "wide":                                   # above every sampled key: the last cell
+        return np.uint32(0x80000000) | full
     if kind == "largest":
         return np.uint32(0xFFFFFFFF) - (full & np.uint32(0x3FF))
     return base + (full & np.uint32({"digit": 0xFF, "digits": 0x3FFFF, "middle": 0xFF00}[kind]))
@@ -94,7 +96,7 @@ def _unseen(full: np.ndarray, kind: str) -> np.ndarray:
 # cells near the tile of k_cells (10240 keys, 8192 pairs) and the sweeps' tile (6144), and the longest
 @pytest.mark.parametrize("rank_mode", [0, 1])
 @pytest.mark.parametrize("pairs", [False, True])
-@pytest.mark.parametrize("kind", ["value", "two_values", "digit", "digits", "middle", "largest"])
+@pytest.mark.parametrize("kind", ["value", "two_values", "digit", "digits", "middle", "largest", "wide"])
 def test_off_the_salted_positions(kind, pairs, rank_mode):
     torch = torch_cuda()
     from paper_cs_0004013_amd import binding
@@ -103,7 +105,8 @@ def test_off_the_salted_positions(kind, pairs, rank_mode):
         for n in ([9_300, 13_312, 13_313, 70_001, 5 << 17] if pairs else [16_385, 19_456, 19_457, 100_003, 9 << 17]):
             full = _full(n)
             t_in, _ = to_dev(full, n % 4)
-            keys = _off_sample(full, _salt(t_in.data_ptr()), _unseen(full, kind))
+            seen = full >> np.uint32(2) if kind == "wide" else full
+            keys = _off_sample(seen, _salt(t_in.data_ptr()), _unseen(full, kind))
             t_in.copy_(torch.from_numpy(keys.view(np.int32)))
             inplace = bool(n & 1)
             t_out = t_in if inplace else torch.empty_like(t_in)
